@@ -39,7 +39,7 @@ constexpr int kDtF64 = 100;  // operand code of the internal fp64 arrays
 constexpr int kGT = 64;      // GEMM output tile (rows and columns)
 constexpr int kGK = 32;      // GEMM K per LDS stage
 constexpr int kEigThreads = 1024;
-constexpr int kCholThreads = 1024;  // CholQR: one workgroup (fewer threads were slower at b = 120)
+constexpr int kCholThreads = 1024;  // CholQR of blocks past kPackMax: one workgroup
 constexpr int kMaxBlock = 1024;     // largest eigenproblem: one workgroup, one pair per thread
 constexpr int kEigLdsMax = 128;     // b <= 128: the matrix stays in LDS during the sweeps
 constexpr int kPackMax = 192;       // b <= 192: one triangle of it stays in LDS (b (b + 1) / 2 doubles)
@@ -580,36 +580,22 @@ __global__ __launch_bounds__(kApplyThreads) void rot_apply_kernel(const double2*
   }
 }
 
-// Orthonormalisation by Cholesky (CholQR): for the Gram matrix G = Y^T Y
-// [b x b], G = L L^T (lower, in place in G's lower triangle), then T = L^-T
-// (upper) into T, so that Q = Y T has orthonormal columns.  A pivot <= 1e-13
-// of the largest diagonal entry is dropped (that column of L and of L^-1 is
-// zero), so a rank-deficient block gives zero columns instead of a breakdown.
-// X = L^-1 (lower triangular) is computed by right-looking forward
-// substitution; its diagonal is 1 / L_kk.  One workgroup.  When b <=
-// kEigLdsMax everything stays in LDS: L in the lower triangle of one b x b
-// array and the strict lower part of X, flipped, in its upper triangle
-// (X[i][c] at [b-1-i][b-1-c], c < i, so that a row of X is contiguous); column
-// k of L is copied to a vector while it is scaled.  Else G and the scratch X
-// [b x b] are used in global memory.
-// factor_only (LDS variant): stop after the factorisation and write L to T
-// with 1 / L_kk on its diagonal (for chol_solve_kernel).
-template <bool kLds>
-__global__ __launch_bounds__(kCholThreads) void chol_orth_kernel(double* G, double* X, double* T, int b,
-                                                                 int factor_only) {
-  extern __shared__ double chol_smem[];
+// Orthonormalisation by Cholesky (CholQR) for b > kPackMax: for the Gram
+// matrix G = Y^T Y [b x b], G = L L^T (lower, in place in G's lower triangle),
+// then T = L^-T (upper) into T, so that Q = Y T has orthonormal columns.  A
+// pivot <= 1e-13 of the largest diagonal entry is dropped (that column of L
+// and of L^-1 is zero), so a rank-deficient block gives zero columns instead
+// of a breakdown.  X = L^-1 (lower triangular, scratch [b x b]) is computed by
+// right-looking forward substitution.  One workgroup.
+__global__ __launch_bounds__(kCholThreads) void chol_orth_kernel(double* L, double* X, double* T, int b) {
   __shared__ double invs[kMaxBlock];
   __shared__ double colk[kMaxBlock];
   __shared__ double thr;
   const int tid = threadIdx.x;
-  double* L = kLds ? chol_smem : G;
-  if (kLds)
-    for (int e = tid; e < b * b; e += kCholThreads) L[e] = G[e];
-  else
-    for (int e = tid; e < b * b; e += kCholThreads) X[e] = (e / b == e % b) ? 1.0 : 0.0;
+  for (int e = tid; e < b * b; e += kCholThreads) X[e] = (e / b == e % b) ? 1.0 : 0.0;
   if (tid == 0) {
     double mx = 0.0;
-    for (int i = 0; i < b; ++i) mx = fmax(mx, G[static_cast<int64_t>(i) * b + i]);
+    for (int i = 0; i < b; ++i) mx = fmax(mx, L[static_cast<int64_t>(i) * b + i]);
     thr = 1e-13 * mx;
   }
   __syncthreads();
@@ -631,55 +617,157 @@ __global__ __launch_bounds__(kCholThreads) void chol_orth_kernel(double* G, doub
     }
     __syncthreads();
   }
-  if constexpr (kLds) {
-    if (factor_only) {
-      for (int e = tid; e < b * b; e += kCholThreads) {
-        const int i = e / b, j = e - i * b;
-        T[e] = j < i ? L[e] : (j == i ? invs[i] : 0.0);
-      }
-      return;
-    }
-    const int b1 = b - 1;
-    // X's strict lower part (in the upper triangle) starts at 0
-    for (int e = tid; e < b * b; e += kCholThreads)
-      if (e % b > e / b) L[e] = 0.0;
-    for (int i = tid; i < b; i += kCholThreads) colk[i] = 0.0;
+  for (int k = 0; k < b; ++k) {
+    const double inv = invs[k];
+    for (int c = tid; c <= k; c += kCholThreads) X[static_cast<int64_t>(k) * b + c] *= inv;
     __syncthreads();
-    // row k of X: X[k][c] = invs[k] * (updated right-hand side), c <= k (the
-    // diagonal is invs[k] itself); the rows below subtract L_ik times it
-    for (int k = 0; k < b; ++k) {
-      const double inv = invs[k];
-      double* xk = L + (b1 - k) * b + b1;  // X[k][c] at xk[-c]
-      for (int c = tid; c < k; c += kCholThreads) xk[-c] *= inv;
-      for (int i = k + 1 + tid; i < b; i += kCholThreads) colk[i] = L[i * b + k];
-      __syncthreads();
-      for (int i = k + 1 + (tid >> 5); i < b; i += kCholThreads / 32) {
-        const double lik = colk[i];
-        double* xi = L + (b1 - i) * b + b1;
-        for (int c = tid & 31; c <= k; c += 32) xi[-c] -= lik * (c < k ? xk[-c] : inv);
+    const int w = b - k - 1;
+    for (int e = tid; e < w * (k + 1); e += kCholThreads) {
+      const int i = k + 1 + e / (k + 1), c = e % (k + 1);
+      X[static_cast<int64_t>(i) * b + c] -= L[i * b + k] * X[static_cast<int64_t>(k) * b + c];
+    }
+    __syncthreads();
+  }
+  for (int e = tid; e < b * b; e += kCholThreads) {
+    const int j = e / b, k = e % b;
+    T[e] = X[static_cast<int64_t>(k) * b + j];
+  }
+}
+
+// CholQR for b <= kPackMax in two kernels on 16 x 16 tiles: chol_factor_kernel
+// (one workgroup, G = L L^T) and chol_trsm_kernel (Q = Y L^-T, 16 rows a wave).
+//
+// What bounds the factorisation is its serial chain: one column at a time with
+// a barrier before and after each (1 us a column, of which the products are a
+// few percent) took 121 us at b = 120 and 279 us at b = 192.  In tiles only the
+// 16 columns of a panel are serial, and they need no barrier and no LDS: every
+// wave that owns rows of the panel holds the diagonal tile's rows in lanes 0-15
+// and 48 rows below in lanes 16-63, one row a lane in registers; a step scales
+// the column by 1 / sqrt(pivot) and subtracts it from the later ones, whose
+// multipliers l_jk are read from the diagonal lanes with v_readlane.  The same
+// operations on the rows of an identity tile give the inverse of the diagonal
+// tile (column c of it in lane c), which the solve needs.  Then the trailing
+// tiles take their update on the fp64 matrix cores: two barriers per 16
+// columns instead of 32.  b = 120: 34 us a call (the 4096 x 4096 conversion,
+// with the solve, 20.0 -> 15.0 ms).
+//
+// LDS: the lower tiles (i, j <= i) at tri_lo(i, j), column-major within a tile
+// (the row fastest), which every access walks without bank conflicts.  Out:
+// Lt[k][i] = L[i][k] (i > k, row stride b) and Inv[16 t + k][m] = element (m, k)
+// of the inverse of diagonal tile t (row stride min(b, 16)).
+constexpr int kFacThreads = 1024;
+constexpr int kTl = 16;                  // tile edge
+constexpr int kTile = kTl * kTl;
+constexpr int kFacRows = 48;             // panel rows per wave (lanes 16-63)
+
+__host__ __device__ __forceinline__ int tri_lo(int i, int j) { return ((i * (i + 1)) >> 1) + j; }
+int chol_tiles(int b) { return (b + kTl - 1) / kTl; }
+int chol_smem_bytes(int b) { return static_cast<int>(sizeof(double)) * kTile * tri_lo(chol_tiles(b), 0); }
+
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(u & 0xffffffffu), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane);
+  return __longlong_as_double((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// 1 / sqrt(d) for a normal d > 0: the hardware estimate (relative error about
+// 2^-26) and one step of the cubically convergent iteration y (1 + e / 2 + 3
+// e^2 / 8), e = 1 - d y^2, which leaves the rounding errors of its last two
+// operations
+__device__ __forceinline__ double rsqrt_f64(double d) {
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-d * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+__global__ __launch_bounds__(kFacThreads) void chol_factor_kernel(const double* __restrict__ G,
+                                                                  double* __restrict__ Lt, double* __restrict__ Inv,
+                                                                  int b) {
+  extern __shared__ double cf_smem[];
+  __shared__ double wmax[kFacThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n16 = lane & 15, gq = lane >> 4;
+  const int nt = (b + kTl - 1) / kTl;
+  const int iw = min(b, kTl);  // row stride of Inv
+  // the lower tiles (zero past b): element (16 i + m, 16 j + k) from G's
+  // mirrored entry, contiguous in m
+  for (int i = 0; i < nt; ++i)
+    for (int e = tid; e < (i + 1) * kTile; e += kFacThreads) {
+      const int m = kTl * i + (e & 15), k = e >> 4;  // k: column 0 .. 16 (i + 1) - 1
+      cf_smem[tri_lo(i, 0) * kTile + e] = m < b && k < b ? G[static_cast<int64_t>(k) * b + m] : 0.0;
+    }
+  double mx = 0.0;
+  if (tid < b) mx = fmax(mx, G[static_cast<int64_t>(tid) * b + tid]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+  if (lane == 0) wmax[wave] = mx;
+  __syncthreads();
+  for (int w = 0; w < kFacThreads / 64; ++w) mx = fmax(mx, wmax[w]);
+  const double thr = 1e-13 * mx;
+
+  for (int kb = 0; kb < nt; ++kb) {
+    // the panel: lanes 0-15 the diagonal tile's rows, lanes 16-63 three of the
+    // row tiles kb + 1 .. nt (tile nt stands for the identity)
+    const int rt = gq == 0 ? kb : kb + 3 * wave + gq;
+    if (kb + 3 * wave + 1 <= nt) {
+      const double* src = cf_smem + tri_lo(rt < nt ? rt : kb, kb) * kTile + n16;
+      double v[kTl];
+#pragma unroll
+      for (int k = 0; k < kTl; ++k) {
+        const double a = src[k * kTl];
+        v[k] = rt < nt ? a : (k == n16 ? 1.0 : 0.0);
       }
-      __syncthreads();
-    }
-    for (int e = tid; e < b * b; e += kCholThreads) {
-      const int j = e / b, k = e % b;  // T[j][k] = X[k][j]
-      T[e] = j < k ? L[(b1 - k) * b + (b1 - j)] : (j == k ? invs[k] : 0.0);
-    }
-  } else {
-    for (int k = 0; k < b; ++k) {
-      const double inv = invs[k];
-      for (int c = tid; c <= k; c += kCholThreads) X[static_cast<int64_t>(k) * b + c] *= inv;
-      __syncthreads();
-      const int w = b - k - 1;
-      for (int e = tid; e < w * (k + 1); e += kCholThreads) {
-        const int i = k + 1 + e / (k + 1), c = e % (k + 1);
-        X[static_cast<int64_t>(i) * b + c] -= L[i * b + k] * X[static_cast<int64_t>(k) * b + c];
+      double invd = 0.0;  // lane k < 16: the reciprocal of pivot k's root
+#pragma unroll
+      for (int k = 0; k < kTl; ++k) {
+        const double d = readlane_f64(v[k], k);
+        const double inv = d > thr ? rsqrt_f64(d) : 0.0;
+        v[k] *= inv;
+#pragma unroll
+        for (int j = k + 1; j < kTl; ++j) v[j] = fma(-readlane_f64(v[k], j), v[k], v[j]);
+        if (lane == k) invd = inv;
       }
-      __syncthreads();
+      const int row = kTl * rt + n16;
+      if (gq == 0) {
+        if (wave == 0 && row < b) {
+#pragma unroll
+          for (int k = 0; k < kTl; ++k)
+            if (k < n16) Lt[static_cast<int64_t>(kTl * kb + k) * b + row] = v[k];
+          Lt[static_cast<int64_t>(row) * b + row] = invd;
+        }
+      } else if (rt < nt) {
+        double* dst = cf_smem + tri_lo(rt, kb) * kTile + n16;
+#pragma unroll
+        for (int k = 0; k < kTl; ++k) {
+          dst[k * kTl] = v[k];
+          if (row < b) Lt[static_cast<int64_t>(kTl * kb + k) * b + row] = v[k];
+        }
+      } else if (rt == nt && kTl * kb + n16 < b) {
+        // lane c holds column c of the inverse
+#pragma unroll
+        for (int m = 0; m < kTl; ++m)
+          if (m < iw) Inv[static_cast<int64_t>(kTl * kb + n16) * iw + m] = v[m];
+      }
     }
-    for (int e = tid; e < b * b; e += kCholThreads) {
-      const int j = e / b, k = e % b;
-      T[e] = X[static_cast<int64_t>(k) * b + j];
+    __syncthreads();
+    // trailing tiles (i, j), kb < j <= i: C_ij -= L_i L_j^T, as D'[col][row]
+    const int n = nt - 1 - kb;
+    int i = 0, j = wave;
+    while (j > i) j -= ++i;
+    for (int t = wave; t < n * (n + 1) / 2; t += kFacThreads / 64) {
+      double* c = cf_smem + tri_lo(kb + 1 + i, kb + 1 + j) * kTile + lane;
+      const double* li = cf_smem + tri_lo(kb + 1 + i, kb) * kTile + lane;
+      const double* lj = cf_smem + tri_lo(kb + 1 + j, kb) * kTile + lane;
+      d4 acc = {c[0], c[64], c[128], c[192]};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-lj[64 * s], li[64 * s], acc, 0, 0, 0);
+      c[0] = acc[0], c[64] = acc[1], c[128] = acc[2], c[192] = acc[3];
+      for (j += kFacThreads / 64; j > i;) j -= ++i;
     }
+    __syncthreads();
   }
 }
 
@@ -772,145 +860,84 @@ __global__ __launch_bounds__(kEigThreads) void top_eig_kernel(const double* A, d
   if (tid == 0) lam[0] = lambda;
 }
 
-// Q = Y L^-T for CholQR with b <= kPackMax, row by row: q L^T = y, so
-// q_k = (y_k - sum_{c<k} q_c L_kc) / L_kk.  64 rows per workgroup, 16 lanes
-// per row (one DPP row): lane t holds y_c and q_c for c = t + 16 j in
-// registers (the steps are unrolled, so the slot j is a constant), its part
-// of each sum is added over the row by DPP, and the lane that holds y_k
-// computes q_k; no LDS traffic or barrier per step.  L (lower, 1 / L_kk on
-// the diagonal, as chol_orth_kernel's factor_only output) as its packed lower
-// triangle in LDS.
-constexpr int kSolveRows = 64;
+// Q = Y L^-T for CholQR with b <= kPackMax from chol_factor_kernel's Lt and Inv.
+// A wave takes 16 rows as the columns of Q^T = L^-1 Y^T: it holds them as fp64
+// matrix-core accumulators, lane (n16, gq) element 16 j + 4 v + gq of row n16,
+// which is the layout of the same instruction's B operand, so a finished tile
+// q_i = Inv_i y_i goes straight into the updates y_j -= L_ji q_i of the tiles
+// below it.  L's tiles (negated) and the inverses of its diagonal tiles are
+// staged in LDS in A-operand order.  Row by row with one DPP sum per column the
+// solve took 39 us at 4096 x 120 and 189 us at 11008 x 192: a chain of b
+// dependent sums; here the chain is 8 matrix instructions per 16 columns (4096
+// x 120: 25 us).
+constexpr int kSolveThreads = 256;
+constexpr int kSolveRows = kSolveThreads / 64 * kTl;
+constexpr int kSolveBatch = 12;  // tiles whose loads a thread has in flight
 
-// a double moved across lanes by a DPP control (both 32-bit halves)
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const uint64_t u = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u & 0xffffffffu), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double((static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo));
-}
-// the sum over the 16 lanes of a DPP row, in every lane (quad swaps, then the
-// half-row and row mirrors)
-__device__ __forceinline__ double row16_sum(double v) {
-  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-  v += dpp_f64<0x141>(v);  // row_half_mirror
-  v += dpp_f64<0x140>(v);  // row_mirror
-  return v;
-}
-
-template <int kSolveSlots>  // b <= 16 kSolveSlots
-__global__ __launch_bounds__(kCholThreads) void chol_solve_kernel(const double* Y, const double* Lf, double* Q,
-                                                                  int rows, int b) {
-  extern __shared__ double sv_smem[];
-  double* Lp = sv_smem;  // tri_lo
-  const int tid = threadIdx.x;
-  for (int i = tid >> 5; i < b; i += kCholThreads / 32)
-    for (int j = tid & 31; j <= i; j += 32) Lp[((i * (i + 1)) >> 1) + j] = Lf[static_cast<int64_t>(i) * b + j];
-  const int t = tid & 15;
-  const int row = blockIdx.x * kSolveRows + (tid >> 4);
+template <int NT>  // b <= 16 NT
+__global__ __launch_bounds__(kSolveThreads) void chol_trsm_kernel(const double* __restrict__ Y,
+                                                                  const double* __restrict__ Lt,
+                                                                  const double* __restrict__ Inv,
+                                                                  double* __restrict__ Q, int rows, int b) {
+  extern __shared__ double tr_smem[];  // tiles at tri_lo(i, j)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int n16 = lane & 15, gq = lane >> 4;
+  const int nt = (b + kTl - 1) / kTl;
+  const int iw = min(b, kTl);
+  const int row = blockIdx.x * kSolveRows + (tid >> 6) * kTl + n16;
   const bool ok = row < rows;
-  double q[kSolveSlots];
+  d4 y[NT];
 #pragma unroll
-  for (int j = 0; j < kSolveSlots; ++j) {
-    const int c = t + 16 * j;
-    q[j] = ok && c < b ? Y[static_cast<int64_t>(row) * b + c] : 0.0;  // y, replaced by q step by step
-  }
-  __syncthreads();
+  for (int j = 0; j < NT; ++j)
 #pragma unroll
-  for (int kb = 0; kb < kSolveSlots; ++kb) {
+    for (int v = 0; v < 4; ++v) {
+      const int c = kTl * j + 4 * v + gq;
+      const bool in = ok && c < b;
+      const double a = Y[in ? static_cast<int64_t>(row) * b + c : 0];
+      y[j][v] = in ? a : 0.0;
+    }
+  {
+    const int m = tid & 15, k = tid >> 4;
+    const int ntl = tri_lo(nt, 0);
+    int i = 0, j = 0;
+    for (int t0 = 0; t0 < ntl; t0 += kSolveBatch) {
+      double w[kSolveBatch];
 #pragma unroll
-    for (int t0 = 0; t0 < 16; ++t0) {
-      const int k = 16 * kb + t0;
-      if (k >= b) break;
-      const double* lk = Lp + ((k * (k + 1)) >> 1);
-      double s = 0.0;
-#pragma unroll
-      for (int j = 0; j <= kb; ++j) {
-        const int c = t + 16 * j;
-        if (c < k) s += q[j] * lk[c];
+      for (int u = 0; u < kSolveBatch; ++u) {
+        const bool dg = i == j, on = t0 + u < ntl && kTl * j + k < b && (dg ? m < iw : kTl * i + m < b);
+        const int64_t e = dg ? static_cast<int64_t>(kTl * i + k) * iw + m
+                             : static_cast<int64_t>(kTl * j + k) * b + kTl * i + m;
+        const double a = (dg ? Inv : Lt)[on ? e : 0];
+        w[u] = on ? (dg ? a : -a) : 0.0;
+        if (++j > i) ++i, j = 0;
       }
-      s = row16_sum(s);
-      if (t == t0) q[kb] = (q[kb] - s) * lk[k];
-    }
-  }
 #pragma unroll
-  for (int j = 0; j < kSolveSlots; ++j) {
-    const int c = t + 16 * j;
-    if (ok && c < b) Q[static_cast<int64_t>(row) * b + c] = q[j];
-  }
-}
-
-// CholQR for kEigLdsMax < b <= kPackMax (factor_only: stop after the
-// factorisation, as chol_orth_kernel): L as its lower triangle in LDS (row
-// i holds columns 0 .. i), factorised as in chol_orth_kernel; then L^-1 in
-// place, from the last column to the first: column j of L^-1 below the
-// diagonal is -(1 / L_jj) times the already inverted trailing block applied to
-// column j of L (each row's sum on 32 lanes); the diagonal is 1 / L_jj (0 for
-// a dropped pivot, whose row and column of L^-1 are then 0).  T = L^-T.
-__device__ __forceinline__ int tri_lo(int i, int j) { return ((i * (i + 1)) >> 1) + j; }
-
-__global__ __launch_bounds__(kCholThreads) void chol_orth_packed_kernel(const double* G, double* T, int b,
-                                                                        int factor_only) {
-  extern __shared__ double chol_smem[];
-  __shared__ double invs[kPackMax];
-  __shared__ double colk[kPackMax];
-  __shared__ double thr;
-  const int tid = threadIdx.x;
-  const int lane32 = tid & 31;
-  double* L = chol_smem;  // tri_lo
-  for (int i = tid >> 5; i < b; i += kCholThreads / 32)
-    for (int j = lane32; j <= i; j += 32) L[tri_lo(i, j)] = G[static_cast<int64_t>(i) * b + j];
-  if (tid == 0) {
-    double mx = 0.0;
-    for (int i = 0; i < b; ++i) mx = fmax(mx, G[static_cast<int64_t>(i) * b + i]);
-    thr = 1e-13 * mx;
+      for (int u = 0; u < kSolveBatch; ++u)
+        if (t0 + u < ntl) tr_smem[(t0 + u) * kTile + tid] = w[u];
+    }
   }
   __syncthreads();
-  for (int k = 0; k < b; ++k) {
-    const double d = L[tri_lo(k, k)];
-    const double inv = d > thr ? 1.0 / sqrt(d) : 0.0;
-    if (tid == 0) invs[k] = inv;
-    for (int i = k + 1 + tid; i < b; i += kCholThreads) {
-      const double v = L[tri_lo(i, k)] * inv;
-      L[tri_lo(i, k)] = v;
-      colk[i] = v;
-    }
-    __syncthreads();
-    for (int i = k + 1 + (tid >> 5); i < b; i += kCholThreads / 32) {
-      const double lik = colk[i];
-      double* row = L + tri_lo(i, 0);
-      for (int j = k + 1 + lane32; j <= i; j += 32) row[j] -= lik * colk[j];
-    }
-    __syncthreads();
-  }
-  for (int i = tid; i < b; i += kCholThreads) L[tri_lo(i, i)] = invs[i];
-  __syncthreads();
-  if (factor_only) {
-    // L with 1 / L_kk on its diagonal, for chol_solve_kernel
-    for (int e = tid; e < b * b; e += kCholThreads) {
-      const int i = e / b, j = e - i * b;
-      T[e] = j <= i ? L[tri_lo(i, j)] : 0.0;
-    }
-    return;
-  }
-  for (int j = b - 1; j >= 0; --j) {
-    for (int i = j + 1 + tid; i < b; i += kCholThreads) colk[i] = L[tri_lo(i, j)];
-    __syncthreads();
-    for (int i = j + 1 + (tid >> 5); i < b; i += kCholThreads / 32) {
-      const double* row = L + tri_lo(i, 0);
-      double acc = 0.0;
-      for (int c = j + 1 + lane32; c <= i; c += 32) acc += row[c] * colk[c];
 #pragma unroll
-      for (int o = 16; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
-      if (lane32 == 0) L[tri_lo(i, j)] = -invs[j] * acc;
+  for (int i = 0; i < NT; ++i) {
+    if (i < nt) {
+      const double* inv = tr_smem + tri_lo(i, i) * kTile + lane;
+      d4 q = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) q = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[64 * s], y[i][s], q, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int c = kTl * i + 4 * v + gq;
+        if (ok && c < b) Q[static_cast<int64_t>(row) * b + c] = q[v];
+      }
+#pragma unroll
+      for (int j = i + 1; j < NT; ++j) {
+        if (j < nt) {
+          const double* l = tr_smem + tri_lo(j, i) * kTile + lane;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) y[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(l[64 * s], q[s], y[j], 0, 0, 0);
+        }
+      }
     }
-    __syncthreads();
-  }
-  for (int e = tid; e < b * b; e += kCholThreads) {
-    const int jj = e / b, k = e - jj * b;  // T[jj][k] = X[k][jj]
-    T[e] = jj <= k ? L[tri_lo(k, jj)] : 0.0;
   }
 }
 
@@ -1212,55 +1239,31 @@ struct Svid {
   // Y^T Y = L L^T, Qo = Y L^-T (dropped pivots give zero columns); the
   // columns are orthonormal up to about cond(Y)^2 times the rounding unit,
   // which is all the iteration needs
-  // Qo = Y L^-T from the factor chol_orth_*_kernel left in L.e (b <= kPackMax)
-  hipError_t solve(const double* Y, double* Qo, int rows, int b) const {
-    const int smem = static_cast<int>(sizeof(double) * b * (b + 1) / 2);
-    const void* fn = b <= 128 ? reinterpret_cast<const void*>(&chol_solve_kernel<8>)
-                              : reinterpret_cast<const void*>(&chol_solve_kernel<12>);
-    if (smem > 65536) {
-      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-      if (e != hipSuccess) return e;
-    }
-    const dim3 grid((rows + kSolveRows - 1) / kSolveRows);
-    if (b <= 128)
-      hipLaunchKernelGGL(chol_solve_kernel<8>, grid, dim3(kCholThreads), smem, st, Y,
-                         static_cast<const double*>(at(L.e)), Qo, rows, b);
-    else
-      hipLaunchKernelGGL(chol_solve_kernel<12>, grid, dim3(kCholThreads), smem, st, Y,
-                         static_cast<const double*>(at(L.e)), Qo, rows, b);
-    return hipGetLastError();
-  }
-
   hipError_t orth_chol(const double* Y, double* Qo, int rows) const {
     const int b = L.b;
     hipError_t e;
     if ((e = mm(Y, kDtF64, 1, b, false, Y, kDtF64, b, 1, false, at(L.gram), b, b, b, rows)) != hipSuccess) return e;
-    if (b <= kEigLdsMax) {
-      const int smem = static_cast<int>(sizeof(double) * b * b);
+    if (b <= kPackMax) {
+      const int smem = chol_smem_bytes(b);
+      const void* solve = b <= 128 ? reinterpret_cast<const void*>(&chol_trsm_kernel<8>)
+                                   : reinterpret_cast<const void*>(&chol_trsm_kernel<12>);
       if (smem > 65536) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chol_orth_kernel<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
+        for (const void* fn : {reinterpret_cast<const void*>(&chol_factor_kernel), solve})
+          if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, smem)) != hipSuccess) return e;
       }
-      hipLaunchKernelGGL((chol_orth_kernel<true>), dim3(1), dim3(kCholThreads), smem, st, at(L.gram), at(L.et),
-                         at(L.e), b, 1);
+      hipLaunchKernelGGL(chol_factor_kernel, dim3(1), dim3(kFacThreads), smem, st,
+                         static_cast<const double*>(at(L.gram)), at(L.e), at(L.et), b);
       if ((e = hipGetLastError()) != hipSuccess) return e;
-      return solve(Y, Qo, rows, b);
-    } else if (b <= kPackMax) {
-      const int smem = static_cast<int>(sizeof(double) * b * (b + 1) / 2);
-      if (smem > 65536) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chol_orth_packed_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
-      }
-      hipLaunchKernelGGL(chol_orth_packed_kernel, dim3(1), dim3(kCholThreads), smem, st,
-                         static_cast<const double*>(at(L.gram)), at(L.e), b, 1);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      return solve(Y, Qo, rows, b);
-    } else {
-      hipLaunchKernelGGL((chol_orth_kernel<false>), dim3(1), dim3(kCholThreads), 0, st, at(L.gram), at(L.et),
-                         at(L.e), b, 0);
+      const dim3 grid((rows + kSolveRows - 1) / kSolveRows);
+      if (b <= 128)
+        hipLaunchKernelGGL(chol_trsm_kernel<8>, grid, dim3(kSolveThreads), smem, st, Y,
+                           static_cast<const double*>(at(L.e)), static_cast<const double*>(at(L.et)), Qo, rows, b);
+      else
+        hipLaunchKernelGGL(chol_trsm_kernel<12>, grid, dim3(kSolveThreads), smem, st, Y,
+                           static_cast<const double*>(at(L.e)), static_cast<const double*>(at(L.et)), Qo, rows, b);
+      return hipGetLastError();
     }
+    hipLaunchKernelGGL(chol_orth_kernel, dim3(1), dim3(kCholThreads), 0, st, at(L.gram), at(L.et), at(L.e), b);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return mm(Y, kDtF64, b, 1, false, at(L.e), kDtF64, b, 1, false, Qo, b, rows, b, b);
   }

@@ -89,6 +89,22 @@ def test_dual_svid_matches_oracle(case):
     _check_path(got, ref, 1, f"{case} path 1")
 
 
+# (d_out, d_in, r, oversample): blocks b = r + oversample at the edges of the 16-wide tiles of the tiled
+# Cholesky and triangular solve, the smallest, and the largest of each of their two sizes (128, 192)
+EDGES = [(40, 30, 1, 0), (40, 30, 15, 0), (30, 40, 16, 0), (40, 35, 16, 1), (70, 65, 48, 1), (150, 128, 112, 16),
+         (208, 192, 176, 16)]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=[f"b{c[2] + c[3]}" for c in EDGES])
+def test_dual_svid_block_edges(case):
+    d_out, d_in, r, over = case
+    W = synth.dense_weight(d_out, d_in, r, 0.002, cfg=71, linear=d_out + d_in)
+    ref = O.dual_svid(W.astype(np.float64), r)
+    got = _run(W, r, oversample=over, iters=40)
+    _check_path(got, ref, 0, f"{case} path 0")
+    assert np.abs(got["W_res"] - ref["Wres"]).max() <= TOL * np.abs(W).max()
+
+
 @pytest.mark.parametrize("d_out,d_in,r", [(64, 32, 4), (128, 128, 16), (32, 128, 8)])
 def test_dual_svid_exact_family(d_out, d_in, r):
     # Dual-SVID recovers a weight built as one LittleBit path exactly; the residual is ~0
