@@ -67,6 +67,28 @@ def test_pack_bit_exact(rows, r, dt):
         assert got.cpu().numpy().tobytes() == ref.tobytes(), (rows, r, dt, role)
 
 
+@pytest.mark.parametrize("rows,r", [(1, 63), (15, 64), (16, 65), (17, 48), (31, 49), (48, 129), (49, 3)])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_pack_tile_edges(rows, r, dt):
+    # 16-row and 64-latent wave tiles, the 16- and 32-bit tail planes, NaNs and infinities in the last row and column;
+    # the source is a view that starts one element into its buffer
+    rs = np.random.default_rng(rows * 131 + r)
+    src64 = rs.standard_normal((rows, r))
+    src64[-1, -1] = np.nan
+    src64[-1, 0] = -np.inf
+    raw = synth.quantize(src64, dt)
+    buf = torch.zeros(rows * r + 1, dtype=U.torch_dtype(dt), device="cuda")
+    src_t = buf[1:].view(rows, r)
+    src_t.copy_(U.raw_to_torch(raw, dt))
+    for role in (lb.LB_ROLE_U, lb.LB_ROLE_V):
+        cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+        got = lb.lb_pack_signs(src_t, role, nan_count=cnt)
+        torch.cuda.synchronize()
+        ref, nans = O.pack(O.to_f64(raw, dt), role)
+        assert got.cpu().numpy().tobytes() == ref.tobytes(), (rows, r, dt, role)
+        assert int(cnt.item()) == nans == 1
+
+
 def test_pack_nan_count():
     src = torch.randn(64, 48, device="cuda")
     src[3, 5] = float("nan")
