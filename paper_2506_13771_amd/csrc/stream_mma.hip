@@ -2,20 +2,20 @@
 // 64 tokens (Proposition 1, Eq. proposition1; both paths summed as in Eq.
 // final_weight_approx_res), in three kinds of launch whatever the list's
 // length, with no workgroup waiting for another:
-//   S1  one workgroup per (linear, path, group of MT tiles of 16 latents, run
-//       of d_in): D[k][t] = sum_j (s(V_p[j][k]) g_p[j]) x[t][j] over the run
-//       with v_mfma_f32_16x16x32_bf16; the bf16 terms of g and x of a 32-input
-//       block are built once and serve every latent tile of the group; the 4
-//       waves split the run's blocks and are summed in a fixed order; the
-//       run's partial sums l (.) z go to the workspace (one launch per token
-//       tile count, 1..4);
-//   R   one thread per (linear, path, token, latent): w = l (.) z, the sum of
-//       the runs' partials in ascending run order, cut into bf16 terms and
-//       stored in the layout of stage 2's B operand;
-//   S2  one workgroup per (linear, 128 output rows for up to 16 tokens, else
-//       256): the rows' U signs in LDS, each 32-latent block's A operand built
-//       once per row tile for every token tile, y = h_0 u_0 + h_1 u_1 rounded
-//       once (one launch per token tile count).
+//   S1  one workgroup per (linear, path, group of latent tiles, run of d_in):
+//       D[k][t] = sum_j (s(V_p[j][k]) g_p[j]) x[t][j] over the run with
+//       v_mfma_f32_16x16x32_bf16; the bf16 terms of the run's g are cut once
+//       into LDS, the 4 waves split the group's latent tiles; the partial sums
+//       go to the workspace in accumulator order (one launch per token tile
+//       count, 1..4);
+//   R   one thread per (linear, path, token tile, 32 latents, lane): w = l (.) z
+//       from the runs' partials in ascending run order, cut into bf16 terms and
+//       stored as stage 2's B operand;
+//   S2  one workgroup per (linear, 256 or 512 output rows): the B operands of both
+//       paths stream through LDS, shared by the 4 waves, each 32-latent block's
+//       A operand (U signs) is built once per row tile and serves every token
+//       tile, y = h_0 u_0 + h_1 u_1 rounded once (one launch per token tile
+//       count).
 // Operands as in the single-launch matrix-core kernel: g and x are cut into
 // exact bf16 terms (1, 2 or 3 per value for bf16, f16, fp32), so every product
 // is exact and the sums are fp32; w is cut into 2 bf16 terms (3 for fp32
@@ -48,143 +48,196 @@ constexpr int kWaves = 4;
 constexpr int kMaxTok = 64;
 constexpr int kMaxRank = 1024;
 constexpr int kMaxRuns = 511;   // S1 map code: 9 bits of run
-constexpr int kMaxGroups = 63;  // S1 map code: 6 bits of latent group
+constexpr int kMaxBpr = 64;     // most 32-input blocks per run (its g terms are held in LDS)
+constexpr int kMinBpr = 8;      // fewest, for lists too short to fill the chip with longer runs
+constexpr int kWantWg1 = 1024;  // S1 workgroups below which runs get shorter
 
-// latent tiles of a group and 32-input blocks of a run, by token tile count
-__host__ __device__ constexpr int mt_of(int tt) { return tt == 1 ? 4 : (tt == 2 ? 8 : 6); }
-__host__ __device__ constexpr int bpr_of(int tt) { return tt == 1 ? 16 : (tt == 2 ? 32 : 64); }
-// blocks a wave loads per round
-__host__ __device__ constexpr int ku_of(int tt) { return tt <= 2 ? 2 : 1; }
+// 16-latent tiles a wave holds: the smallest class that takes the linear in
+// the fewest groups (4 accumulator registers per tile and token tile)
+constexpr int kMtClasses = 4;
+__host__ __device__ constexpr int mt_cls(int tt, int c) {
+  return c == 0 ? 2 : (c == 1 ? 3 : (c == 2 ? 5 : (tt <= 2 ? 8 : 6)));
+}
 
 struct SmGeom {
-  int tt, mt, ng, bpr, s1d;
+  int tt, nmf, ng, mt, bpr, s1d;
+  int cls;  // launch of S1: (tt - 1) kMtClasses + class
 };
 
-SmGeom sm_geometry(const ForwardArgs& a) {
+// bpr: 32-input blocks per run wanted
+SmGeom sm_geometry(const ForwardArgs& a, int bpr) {
   SmGeom g{};
   g.tt = (a.T + 15) / 16;
-  g.mt = mt_of(g.tt);
-  const int nmf = (a.r + 15) / 16;
-  g.ng = (nmf + g.mt - 1) / g.mt;
+  g.nmf = (a.r + 15) / 16;
+  const int most = kWaves * mt_cls(g.tt, kMtClasses - 1);
+  g.ng = (g.nmf + most - 1) / most;
+  const int need = (g.nmf + kWaves * g.ng - 1) / (kWaves * g.ng);
+  int c = 0;
+  while (mt_cls(g.tt, c) < need) ++c;
+  g.mt = need;
+  g.cls = (g.tt - 1) * kMtClasses + c;
   const int nbt = nblocks32(a.d_in);
-  g.bpr = bpr_of(g.tt);
+  g.bpr = std::min(kMaxBpr, std::max(bpr, (nbt + kMaxRuns - 1) / kMaxRuns));
   g.s1d = (nbt + g.bpr - 1) / g.bpr;
   return g;
 }
 
+// partial sums of one linear: [2][s1d][nmf][tt][64 lanes][4] floats
+size_t part_bytes(const SmGeom& g) { return static_cast<size_t>(2) * g.s1d * g.nmf * g.tt * 1024; }
+
 // ---------------------------------------------------------------------------
 // S1
 // ---------------------------------------------------------------------------
-template <int TT, int MT>
-struct BlockLoads {
-  uint32_t w[MT];
-  uint32_t g[2][4];
-  uint32_t x[TT][2][4];
+// low (high) halves of a and b as one register: a's in the low half
+__device__ __forceinline__ uint32_t lo16s(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ uint32_t hi16s(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+typedef __attribute__((address_space(3))) void* lds_ptr;
+
+// at most VM vector-memory operations of this wave outstanding and its LDS
+// accesses done, then the barrier; LDS accesses stay on their side of it
+template <int VM>
+__device__ __forceinline__ void wait_barrier() {
+  static_assert(VM >= 0 && VM < 64, "vmcnt range");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Wave w of a group holds latent tiles t0 + (0 .. mt - 1), t0 = (4 grp + w) mt.
+// x (shared by the waves) and each wave's V words stream through kBuf1 LDS
+// buffers of CB blocks, filled by global-to-LDS loads kBuf1 - 1 chunks ahead:
+// loads into registers had cost the occupancy that was to hide their latency.
+// What bounds it then: building the A operands, 13 VALU instructions per tile
+// and block with f16 scales (2 terms) for 2 matrix instructions per token tile,
+// so up to 16 tokens the VALU, from 32 tokens on the matrix cores.  The g terms
+// are cut once per workgroup (a wave that cut its own spent 40 instructions a
+// block on them), partial sums leave as 16-byte stores, and the waves split the
+// latents, not the blocks, so no sum crosses waves.
+constexpr int kBuf1 = 4;
+__host__ __device__ constexpr int cb_of(int tt) { return tt <= 2 ? 2 : 1; }
+
+// LDS of S1: the run's g terms, the x and V-word buffers, the tail block's
+// words.  One array: of several the compiler would follow each buffer's loads
+// and wait for the newest before every read.
+template <int TT, int MT, int ACT, int SC>
+struct S1Lds {
+  static constexpr int XC = ACT == kDtF32 ? 2 : 1;
+  static constexpr int XI = (cb_of(TT) * TT * XC + kWaves - 1) / kWaves;
+  static constexpr int NV = (MT + 3) / 4;
+  static constexpr int kXbuf = XI * kWaves * 1024;
+  static constexpr int kXs = kMaxBpr * 4 * nterms<SC>() * 16;
+  static constexpr int kVs = kXs + kBuf1 * kXbuf;
+  static constexpr int kVt = kVs + kBuf1 * cb_of(TT) * kWaves * NV * 256;
+  static constexpr int kBytes = kVt + kWaves * NV * 256;
+  static_assert(kBytes <= 65536, "no launch attribute needed");
 };
 
-// loads of block b (valid; else every load reads past the buffers: zeros);
-// lane (n16, gq) reads the words of latents k0 + 16 m + n16 and x, g at
-// inputs 32 b + 4 gq + 16 h + (0..3)
 template <int TT, int MT, int ACT, int SC>
-__device__ __forceinline__ void s1_load(rsrc_t vr, rsrc_t gr, rsrc_t xr, int b, bool valid, int k0, int n16, int gq,
-                                        int r, int d_in, BlockLoads<TT, MT>& L) {
-#pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    const int k = k0 + 16 * m + n16;
-    L.w[m] = __builtin_amdgcn_raw_buffer_load_b32(vr, valid && k < r ? static_cast<uint32_t>(b * r + k) * 4u : kOob,
-                                                  0, 0);
-  }
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const uint32_t j0 = 32 * b + 4 * gq + 16 * h;
-    bload4<SC, true>(gr, j0, valid, L.g[h]);
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-      bload4<ACT, true>(xr, static_cast<uint32_t>(16 * tt + n16) * d_in + j0, valid, L.x[tt][h]);
-  }
-}
-
-// the tail block's word of latent k (tail plane of V_p's packing)
-__device__ __forceinline__ uint32_t s1_tail_word(rsrc_t vr, int k, int r, int d_in, bool valid) {
-  const int nbv = d_in >> 5, tailv = d_in & 31;
-  const uint32_t plane = 4u * nbv * r;
-  const bool ok = valid && k < r;
-  const uint32_t off = tailv <= 16 ? plane + 2u * k : plane + 4u * k;
-  const uint32_t lo = static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(vr, ok ? off : kOob, 0, 0));
-  const uint32_t hi =
-      static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(vr, ok && tailv > 16 ? off + 2 : kOob, 0, 0));
-  return lo | (hi << 16);
-}
-
-// MASK: the tail block, whose x groups at inputs >= d_in belong to the next
-// row and are zeroed (g reads zero there)
-template <int TT, int MT, int ACT, int SC, bool MASK>
-__device__ __forceinline__ void s1_block(const BlockLoads<TT, MT>& L, int b, int gq, int d_in,
-                                         floatx4 (&acc)[MT][TT]) {
+__device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp, int c) {
   constexpr int NG = nterms<SC>(), NX = nterms<ACT>();
-  uint32_t gt[NG][4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    if constexpr (NG == 1) {
-      gt[0][v] = raw16<true>(L.g[0], v) | (raw16<true>(L.g[1], v) << 16);
-    } else {
-      uint32_t lo[NG], hi[NG];
-      split_exact<NG>(raw4_elem<SC, true>(L.g[0], v), lo);
-      split_exact<NG>(raw4_elem<SC, true>(L.g[1], v), hi);
-#pragma unroll
-      for (int s = 0; s < NG; ++s) gt[s][v] = lo[s] | (hi[s] << 16);
-    }
-  }
-  u32x4 X[TT][NX];
-  const bool ok0 = !MASK || 32 * b + 4 * gq < d_in, ok1 = !MASK || 32 * b + 4 * gq + 16 < d_in;
-#pragma unroll
-  for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      if constexpr (NX == 1) {
-        X[tt][0][v] = (ok0 ? raw16<true>(L.x[tt][0], v) : 0u) | ((ok1 ? raw16<true>(L.x[tt][1], v) : 0u) << 16);
-      } else {
-        uint32_t lo[NX], hi[NX];
-        split_exact<NX>(ok0 ? raw4_elem<ACT, true>(L.x[tt][0], v) : 0.0f, lo);
-        split_exact<NX>(ok1 ? raw4_elem<ACT, true>(L.x[tt][1], v) : 0.0f, hi);
-#pragma unroll
-        for (int a = 0; a < NX; ++a) X[tt][a][v] = lo[a] | (hi[a] << 16);
-      }
-    }
-#pragma unroll
-  for (int m = 0; m < MT; ++m)
-#pragma unroll
-    for (int s = 0; s < NG; ++s) {
-      const u32x4 A = sign_terms(L.w[m], gq, gt[s]);
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-        for (int a = 0; a < NX; ++a) acc[m][tt] = mfma(A, X[tt][a], acc[m][tt]);
-    }
-}
-
-template <int TT, int MT, int ACT, int SC>
-__global__ void __launch_bounds__(kThreads) sm_s1_kernel(const uint32_t* __restrict__ hdr,
-                                                         const StreamLinear* __restrict__ descs,
-                                                         const uint32_t* __restrict__ map, uint64_t fp) {
-  constexpr int KU = ku_of(TT);
-  __shared__ floatx4 red[MT * TT * 64];
-  if (!plan_ok(hdr, fp)) return;
-  const uint32_t code = map[blockIdx.x];
-  const StreamLinear& L = descs[code >> 16];
-  const int p = (code >> 15) & 1, grp = (code >> 9) & 63, c = code & 511;
-  const int T = L.T, r = L.r, d_in = L.d_in;
+  constexpr int EX = ACT == kDtF32 ? 4 : 2;
+  constexpr int CB = cb_of(TT);
+  constexpr int XC = EX / 2;                       // 16-byte pieces of a lane's 8 inputs
+  constexpr int kXf = CB * TT * XC;                  // x fragments (1 KB) of a chunk
+  constexpr int XI = (kXf + kWaves - 1) / kWaves;    // of them per wave
+  constexpr int NV = (MT + 3) / 4;                   // word loads (64 latents) per wave and block
+  using Lds = S1Lds<TT, MT, ACT, SC>;
+  extern __shared__ __attribute__((aligned(16))) char sm_lds[];
+  u32x4* gt = reinterpret_cast<u32x4*>(sm_lds);
+  auto xs = [&](int buf) { return reinterpret_cast<u32x4*>(sm_lds + Lds::kXs + buf * Lds::kXbuf); };
+  auto vs = [&](int buf, int bl, int w) {
+    return reinterpret_cast<uint32_t*>(sm_lds + Lds::kVs + ((buf * CB + bl) * kWaves + w) * NV * 256);
+  };
+  uint32_t* vt = reinterpret_cast<uint32_t*>(sm_lds + Lds::kVt) + (threadIdx.x >> 6) * NV * 64;  // this wave's tail words
+  const int T = L.T, r = L.r, d_in = L.d_in, mt = L.mt;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n16 = lane & 15, gq = lane >> 4;
   const rsrc_t vr = make_rsrc_uniform(p ? L.V[1] : L.V[0], L.v_bytes);
   const rsrc_t gr = make_rsrc_uniform(p ? L.g[1] : L.g[0], L.g_bytes);
   const rsrc_t xr = make_rsrc_uniform(L.x, L.x_bytes);
-  const int k0 = 16 * MT * grp;
-  const int nbt = nblocks32(d_in), nbv = d_in >> 5;
+  const int nbt = nblocks32(d_in), nbv = d_in >> 5, tailv = d_in & 31;
   const int b0 = c * L.bpr;
   const int b1 = min(nbt, b0 + L.bpr);
-  const int bf = min(b1, nbv);
+  const int nch = (b1 - b0 + CB - 1) / CB;
+  const int nmf = (r + 15) >> 4;
+  const int t0 = (kWaves * grp + wave) * mt;
+  const int mts = min(mt, nmf - t0);  // this wave's tiles (<= 0: none)
+  const bool xv = d_in % (16 / EX) == 0 && reinterpret_cast<uintptr_t>(L.x) % 16 == 0;
+  const bool tail16 = tailv != 0 && tailv <= 16 && b1 > nbv;  // 16-bit tail words
+
+  // loads of chunk ch into its buffer: every wave issues XI x loads (4 times
+  // as many, of 4 bytes a lane, when rows are not whole 16-byte pieces) and
+  // NV CB word loads, whatever is in range (reads out of it give zeros, so x is
+  // zero past d_in and past T)
+  auto load = [&](int ch) {
+    const int buf = ch % kBuf1, bb = b0 + ch * CB;
+#pragma unroll
+    for (int i = 0; i < XI; ++i) {
+      const int f = wave + kWaves * i;  // (block, token tile, piece), piece fastest
+      const int pc = f % XC, tt = (f / XC) % TT, bl = f / (XC * TT);
+      const bool on = f < kXf && bb + bl < b1;
+      char* dst = reinterpret_cast<char*>(xs(buf) + f * 64);
+      const int j = 32 * (bb + bl) + (4 / XC) * 2 * pc;  // piece pc of lane group gq: inputs j + 8 gq ..
+      if (xv) {
+        const uint32_t off = (static_cast<uint32_t>(16 * tt + n16) * d_in + j + 8 * gq) * EX;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            xr, (lds_ptr)dst, 16, on && 16 * tt + n16 < T && j + 8 * gq < d_in ? off : kOob, 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          // dword lane + 64 d of the fragment: lane (lane + 64 d) / 4 of the 16-byte form, dword % 4 of its piece
+          const int ln = (lane >> 2) + 16 * d;
+          const int row = 16 * tt + (ln & 15), e = j + 8 * (ln >> 4) + (lane & 3) * (4 / EX);
+          const uint32_t off = (static_cast<uint32_t>(row) * d_in + e) * EX;
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_ptr)(dst + 256 * d), 4,
+                                                   on && row < T && e < d_in ? off : kOob, 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int bl = 0; bl < CB; ++bl) {
+      const int b = bb + bl;
+#pragma unroll
+      for (int d = 0; d < NV; ++d) {
+        // 32-bit tail entries sit where a full word would
+        const int k = 16 * t0 + 64 * d + lane;
+        const bool on = b < b1 && (b < nbv || tailv > 16) && k < r;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_ptr)(vs(buf, bl, wave) + 64 * d), 4,
+                                                 on ? static_cast<uint32_t>(b * r + k) * 4u : kOob, 0, 0, 0);
+      }
+    }
+  };
+#pragma unroll
+  for (int ch = 0; ch < kBuf1 - 1; ++ch) load(ch);
+
+  if (tail16)
+#pragma unroll
+    for (int d = 0; d < NV; ++d) {
+      const int k = 16 * t0 + 64 * d + lane;
+      vt[64 * d + lane] = static_cast<uint16_t>(
+          __builtin_amdgcn_raw_buffer_load_b16(vr, k < r ? 4u * nbv * r + 2u * k : kOob, 0, 0));
+    }
+  // the run's g terms (zero past d_in): [block][lane group][term]
+  for (int it = tid; it < (b1 - b0) * 4; it += kThreads) {
+    const uint32_t j0 = 32 * (b0 + (it >> 2)) + 4 * (it & 3);
+    uint32_t raw[2][4];
+    bload4<SC, true>(gr, j0, true, raw[0]);
+    bload4<SC, true>(gr, j0 + 16, true, raw[1]);
+    u32x4 d[NG];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      uint32_t lo[NG], hi[NG];
+      split_exact<NG>(raw4_elem<SC, true>(raw[0], v), lo);
+      split_exact<NG>(raw4_elem<SC, true>(raw[1], v), hi);
+#pragma unroll
+      for (int s = 0; s < NG; ++s) d[s][v] = lo[s] | (hi[s] << 16);
+    }
+#pragma unroll
+    for (int s = 0; s < NG; ++s) gt[it * NG + s] = d[s];
+  }
 
   floatx4 acc[MT][TT];
 #pragma unroll
@@ -192,265 +245,395 @@ __global__ void __launch_bounds__(kThreads) sm_s1_kernel(const uint32_t* __restr
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) acc[m][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // the tail block (if this run holds it, block nbv) goes to wave 0, after its
-  // full blocks (its loads are not held across the main loop)
-  const bool tail = b1 > nbv && wave == 0;
-  // full blocks: wave w takes blocks b0 + KU (w + 4 i) + u
-  for (int rb = b0 + KU * wave; rb < bf; rb += KU * kWaves) {
-    BlockLoads<TT, MT> Lb[KU];
+  // products of block b.  All MT tiles, whether this wave has them or not: a
+  // branch per tile had kept the tiles' operands from overlapping.
+  auto block = [&](int b, int buf, int bl) {
+    u32x4 g[NG];
 #pragma unroll
-    for (int u = 0; u < KU; ++u) s1_load<TT, MT, ACT, SC>(vr, gr, xr, rb + u, rb + u < bf, k0, n16, gq, r, d_in, Lb[u]);
+    for (int s = 0; s < NG; ++s) g[s] = gt[((b - b0) * 4 + gq) * NG + s];
+    const uint32_t* wp = tail16 && b == nbv ? vt : vs(buf, bl, wave);
+    uint32_t words[MT];
 #pragma unroll
-    for (int u = 0; u < KU; ++u) s1_block<TT, MT, ACT, SC, false>(Lb[u], rb + u, gq, d_in, acc);
-  }
-  if (tail) {
-    BlockLoads<TT, MT> LT;
-    s1_load<TT, MT, ACT, SC>(vr, gr, xr, nbv, true, k0, n16, gq, r, d_in, LT);
-#pragma unroll
-    for (int m = 0; m < MT; ++m) LT.w[m] = s1_tail_word(vr, k0 + 16 * m + n16, r, d_in, true);
-    s1_block<TT, MT, ACT, SC, true>(LT, nbv, gq, d_in, acc);
-  }
-
-  // fixed-order sum over the waves: w0 + (w1 + (w2 + w3))
-  for (int w = kWaves - 1; w >= 1; --w) {
-    if (wave == w) {
-#pragma unroll
-      for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-          const int e = (m * TT + tt) * 64 + lane;
-          red[e] = w == kWaves - 1 ? acc[m][tt] : acc[m][tt] + red[e];
-        }
-    }
-    __syncthreads();
-  }
-  if (wave != 0) return;
-  const rsrc_t lr = make_rsrc_uniform(p ? L.l[1] : L.l[0], L.l_bytes);
-#pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    float lk[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) lk[e] = bits_to_f32<SC>(bload<SC>(lr, k0 + 16 * m + 4 * gq + e));
+    for (int m = 0; m < MT; ++m) words[m] = wp[16 * m + n16];
+    u32x4 X[TT][NX];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
-      const floatx4 s = acc[m][tt] + red[(m * TT + tt) * 64 + lane];
-      const int t = 16 * tt + n16;
+      const u32x4* xf = xs(buf) + (bl * TT + tt) * XC * 64;
+      // inputs 4 gq .. + 3 and the same + 16: halves of the pieces of lane groups gq / 2 and gq / 2 + 2
+      uint32_t ra[4] = {0u, 0u, 0u, 0u}, rd[4] = {0u, 0u, 0u, 0u};
+      if constexpr (XC == 1) {
+        const u32x2* x2 = reinterpret_cast<const u32x2*>(xf) + ((gq >> 1) * 16 + n16) * 2 + (gq & 1);
+        const u32x2 a = x2[0], d = x2[64];
+        ra[0] = a[0], ra[1] = a[1], rd[0] = d[0], rd[1] = d[1];
+      } else {
+        const u32x4 a = xf[(gq & 1) * 64 + (gq >> 1) * 16 + n16], d = xf[(gq & 1) * 64 + ((gq >> 1) + 2) * 16 + n16];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = k0 + 16 * m + 4 * gq + e;
-        if (t < T && k < r) L.part[((static_cast<int64_t>(p) * T + t) * L.s1d + c) * r + k] = s[e] * lk[e];
+        for (int v = 0; v < 4; ++v) ra[v] = a[v], rd[v] = d[v];
+      }
+      if constexpr (NX == 1) {
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          X[tt][0][2 * v] = lo16s(ra[v], rd[v]);
+          X[tt][0][2 * v + 1] = hi16s(ra[v], rd[v]);
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          uint32_t lo[NX], hi[NX];
+          split_exact<NX>(raw4_elem<ACT, true>(ra, v), lo);
+          split_exact<NX>(raw4_elem<ACT, true>(rd, v), hi);
+#pragma unroll
+          for (int e = 0; e < NX; ++e) X[tt][e][v] = lo[e] | (hi[e] << 16);
+        }
       }
     }
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const uint32_t ws = words[m] >> (4 * gq);
+      u32x4 sg;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sg[v] = (ws << (15 - v)) & 0x80008000u;
+#pragma unroll
+      for (int s = 0; s < NG; ++s) {
+        const u32x4 A = sg ^ g[s];
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+          for (int e = 0; e < NX; ++e) acc[m][tt] = mfma(A, X[tt][e], acc[m][tt]);
+      }
+    }
+  };
+  constexpr int kAhead = kBuf1 - 2;  // chunks still in flight when one is used
+  for (int ch = 0; ch < nch; ++ch) {
+    // chunk ch has landed (each wave waits for its own loads, the barrier for
+    // everyone's) and every wave is done with the buffer of chunk ch - 1
+    if (xv)
+      wait_barrier<kAhead * (XI + CB * NV)>();
+    else
+      wait_barrier<kAhead * (4 * XI + CB * NV)>();
+    load(ch + kBuf1 - 1);
+    if (mts <= 0) continue;
+#pragma unroll
+    for (int bl = 0; bl < CB; ++bl) {
+      const int b = b0 + ch * CB + bl;
+      if (b < b1) block(b, ch % kBuf1, bl);
+    }
   }
+  // global-to-LDS loads past the run are still in flight: none may land after
+  // the workgroup's LDS is given away
+  __builtin_amdgcn_s_waitcnt(0);
+  if (mts <= 0) return;
+  float* out = L.part + (static_cast<int64_t>(p * L.s1d + c) * nmf + t0) * TT * 256 + lane * 4;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+    if (m < mts)
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) *reinterpret_cast<floatx4*>(out + (m * TT + tt) * 256) = acc[m][tt];
+}
+
+template <int TT, int MT, int ACT, int SC>
+__global__ void __launch_bounds__(kThreads) sm_s1_kernel(const uint32_t* __restrict__ hdr,
+                                                         const StreamLinear* __restrict__ descs,
+                                                         const uint32_t* __restrict__ map, uint64_t fp) {
+  if (!plan_ok(hdr, fp)) return;
+  const uint32_t code = map[blockIdx.x];
+  sm_s1_body<TT, MT, ACT, SC>(descs[code >> 16], (code >> 15) & 1, (code >> 9) & 63, code & 511);
 }
 
 // ---------------------------------------------------------------------------
 // R: w = l (.) z, the runs' partial sums in ascending run order, written as NW
-// bf16 terms straight into the matrix-core B fragments of stage 2: for path
-// p, token tile tt, 32-latent block kb and term a, one u32x4 per lane, lane
-// (n16, gq) register v holding the term of w at token 16 tt + n16 and latents
-// 32 kb + 4 gq + v (low half) and + 16 (high half); tokens past T and latents
-// past r are zero
+// bf16 terms straight into the matrix-core B fragments of stage 2: for path p,
+// 32-latent block kb, token tile tt and term a, one u32x4 per lane, lane (n16,
+// gq) register v holding the term of w at token 16 tt + n16 and latents 32 kb +
+// 4 gq + v (low half) and + 16 (high half); latents past r are zero.  The two
+// accumulator tiles of a block are read as S1's lanes wrote them, so loads and
+// stores are whole 1 KB lines (one element per thread, with 2-byte stores,
+// took 143 us in the 7B, 0.55 bits per weight, 64-token list).
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int nw_of(int act) { return act == kDtF32 ? 3 : 2; }
 
 __host__ __device__ inline size_t frag_bytes(int T, int r, int nw) {
   return static_cast<size_t>(2) * ((T + 15) / 16) * nblocks32(r) * nw * 1024;
 }
+// threads of R for one linear
+__host__ __device__ inline int r_items(int T, int r) { return 2 * ((T + 15) / 16) * nblocks32(r) * 64; }
 
-template <int NW>
+template <int NW, int SC>
+__device__ __forceinline__ void sm_r_body(const StreamLinear& L, int e) {
+  const int T = L.T, r = L.r, s1d = L.s1d;
+  if (e >= r_items(T, r)) return;
+  const int tt_n = (T + 15) / 16, nkb = nblocks32(r), nmf = (r + 15) >> 4;
+  const int lane = e & 63, gq = lane >> 4;
+  const int f = e >> 6;  // (p, kb, tt), tt fastest
+  const int tt = f % tt_n, pk = f / tt_n;
+  const int p = pk >= nkb ? 1 : 0, kb = pk - p * nkb;
+  const bool two = 2 * kb + 1 < nmf;
+  const float* src = L.part + ((static_cast<int64_t>(p) * s1d * nmf + 2 * kb) * tt_n + tt) * 256 + lane * 4;
+  const int64_t cs = static_cast<int64_t>(nmf) * tt_n * 256;
+  const int64_t hs = two ? tt_n * 256 : 0;
+  floatx4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
+#pragma unroll 4
+  for (int c = 0; c < s1d; ++c) {
+    z0 += *reinterpret_cast<const floatx4*>(src + c * cs);
+    z1 += *reinterpret_cast<const floatx4*>(src + c * cs + hs);
+  }
+  const rsrc_t lr = make_rsrc(p ? L.l[1] : L.l[0], L.l_bytes);
+  uint32_t lo[4][NW], hi[4][NW];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int k = 32 * kb + 4 * gq + v;
+    split_round<NW>(k < r ? z0[v] * bits_to_f32<SC>(bload<SC>(lr, k, k < r)) : 0.0f, lo[v]);
+    split_round<NW>(k + 16 < r ? z1[v] * bits_to_f32<SC>(bload<SC>(lr, k + 16, k + 16 < r)) : 0.0f, hi[v]);
+  }
+  u32x4* frag = reinterpret_cast<u32x4*>(L.wlat) + static_cast<int64_t>(f) * NW * 64 + lane;
+#pragma unroll
+  for (int a = 0; a < NW; ++a)
+    frag[a * 64] = u32x4{lo[0][a] | (hi[0][a] << 16), lo[1][a] | (hi[1][a] << 16), lo[2][a] | (hi[2][a] << 16),
+                         lo[3][a] | (hi[3][a] << 16)};
+}
+
+template <int NW, int SC>
 __global__ void __launch_bounds__(kThreads) sm_r_kernel(const uint32_t* __restrict__ hdr,
                                                         const StreamLinear* __restrict__ descs,
                                                         const uint32_t* __restrict__ map, uint64_t fp) {
   if (!plan_ok(hdr, fp)) return;
   const uint32_t code = map[blockIdx.x];
-  const StreamLinear& L = descs[code >> 16];
-  const int e = static_cast<int>(code & 0xffffu) * kThreads + threadIdx.x;
-  const int T = L.T, r = L.r, s1d = L.s1d;
-  const int tt_n = (T + 15) / 16, nkb = nblocks32(r), kp = 32 * nkb;
-  const int per = 16 * tt_n * kp;  // padded (token, latent) slots of one path
-  if (e >= 2 * per) return;
-  const int p = e / per, rem = e - p * per;
-  const int t = rem / kp, k = rem - t * kp;
-  float w = 0.0f;
-  if (t < T && k < r) {
-    const float* src = L.part + (static_cast<int64_t>(p) * T + t) * s1d * r + k;
-    int c = 0;
-    for (; c + 8 <= s1d; c += 8) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = src[static_cast<int64_t>(c + u) * r];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) w += v[u];
-    }
-    for (; c < s1d; ++c) w += src[static_cast<int64_t>(c) * r];
-  }
-  uint32_t terms[NW];
-  split_round<NW>(w, terms);
-  const int tt = t >> 4, n16 = t & 15, kb = k >> 5, kk = k & 31;
-  const int half = kk >> 4, gq = (kk & 15) >> 2, v = kk & 3;
-  uint16_t* frag = reinterpret_cast<uint16_t*>(L.wlat);
-#pragma unroll
-  for (int a = 0; a < NW; ++a) {
-    const int64_t f = ((static_cast<int64_t>(p) * tt_n + tt) * nkb + kb) * NW + a;
-    frag[((f * 64 + gq * 16 + n16) * 4 + v) * 2 + half] = static_cast<uint16_t>(terms[a]);
-  }
+  sm_r_body<NW, SC>(descs[code >> 16], static_cast<int>(code & 0xffffu) * kThreads + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
-// S2: the output rows of one linear, every token, both paths.  Wave w holds
-// RB row tiles of 16 (local rows 16 (w + 4 b) + (0..15)) for every token tile;
-// the A operand of a 32-latent block (the U signs, from LDS) is built once per
-// row tile and serves every token tile.  The B fragments come from R.  (The
-// A operands are what costs VALU time, so the waves split rows, not tokens.)
+// S2: 64 RB output rows of one linear, every token, both paths.  Wave w holds
+// row tiles RB w .. RB w + RB - 1 of 16 rows for every token tile.  The B
+// fragments (shared by the waves) and each wave's U words stream through
+// kBuf2 LDS buffers in chunks of kCk 32-latent blocks (path 0, then path 1),
+// filled by global-to-LDS loads kBuf2 - 1 chunks ahead, one barrier a chunk.
+// Up to 16 tokens the A operands bound it (9 VALU instructions for 2 matrix
+// instructions), from 32 on the matrix cores.
 // ---------------------------------------------------------------------------
-__host__ __device__ constexpr int rb_of(int tt) { return tt == 1 ? 2 : 4; }
-// output rows of a stage-2 workgroup
-__host__ __device__ constexpr int rw_of(int tt) { return 16 * kWaves * rb_of(tt); }
-// U words per thread in flight while staging them in LDS
-constexpr int kStage = 8;
+constexpr int kBuf2 = 3;
+constexpr int kCk = 2;
+// row tiles per wave of the list kernels (fewer, larger workgroups up to 16
+// tokens, where a row tile takes 8 registers; 32 from 49 tokens)
+__host__ __device__ constexpr int rb_of(int tt) { return tt == 1 ? 8 : 4; }
 
-template <int TT, int ACT, int SC>
-__global__ void __launch_bounds__(kThreads) sm_s2_kernel(const uint32_t* __restrict__ hdr,
-                                                         const StreamLinear* __restrict__ descs,
-                                                         const uint32_t* __restrict__ map, uint64_t fp) {
-  constexpr int NW = nw_of(ACT);
-  constexpr int RB = rb_of(TT), RW = rw_of(TT);
-  extern __shared__ uint32_t uwl[];  // [2][nkb][RW] U words of this workgroup's rows
-  if (!plan_ok(hdr, fp)) return;
-  const uint32_t code = map[blockIdx.x];
-  const StreamLinear& L = descs[code >> 16];
-  const int q = static_cast<int>(code & 0xffffu);
+// LDS of S2 (one array, as in S1): the fragment and U-word buffers, the 16-bit
+// tail words
+template <int TT, int RB, int ACT>
+struct S2Lds {
+  static constexpr int FI = (kCk * TT * nw_of(ACT) + kWaves - 1) / kWaves;
+  static constexpr int NV = (RB + 3) / 4;
+  static constexpr int kBbuf = FI * kWaves * 1024;
+  static constexpr int kUs = kBuf2 * kBbuf;
+  static constexpr int kUt = kUs + kBuf2 * kCk * kWaves * NV * 256;
+  static constexpr int kBytes = kUt + 2 * kWaves * NV * 256;
+};
+
+template <int TT, int RB, int ACT, int SC>
+__device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
+  constexpr int NW = nw_of(ACT), CK = kCk;
+  constexpr int kFr = CK * TT * NW;                // fragments (1 KB) of a chunk
+  constexpr int FI = (kFr + kWaves - 1) / kWaves;  // of them per wave
+  constexpr int NV = (RB + 3) / 4;                 // word loads (64 rows) per wave and block
+  using Lds = S2Lds<TT, RB, ACT>;
+  extern __shared__ __attribute__((aligned(16))) char sm_lds[];
+  auto bs = [&](int buf) { return reinterpret_cast<u32x4*>(sm_lds + buf * Lds::kBbuf); };
+  auto us = [&](int buf, int u, int w) {
+    return reinterpret_cast<uint32_t*>(sm_lds + Lds::kUs + ((buf * CK + u) * kWaves + w) * NV * 256);
+  };
+  auto ut = [&](int pp, int w) {  // 16-bit tail words
+    return reinterpret_cast<uint32_t*>(sm_lds + Lds::kUt + (pp * kWaves + w) * NV * 256);
+  };
   const int T = L.T, r = L.r, d_out = L.d_out;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n16 = lane & 15, gq = lane >> 4;
   const int nkb = nblocks32(r), nbu = r >> 5, tailu = r & 31;
-  const int qrow0 = q * RW;
-
-  // the rows' U words (rows past d_out and blocks past r read as zero): a
-  // full word as one 32-bit load, the tail plane's as 16-bit halves; a few
-  // words per thread in flight before they go to LDS
+  const int nch = (nkb + CK - 1) / CK;  // chunks per path
+  const int row0 = (q * kWaves + wave) * 16 * RB;
+  const bool active = row0 < d_out;  // a wave past the last row only loads and keeps the barriers
+  const bool tail16 = tailu != 0 && tailu <= 16;
+  const rsrc_t fr = make_rsrc_uniform(L.wlat, static_cast<uint32_t>(frag_bytes(T, r, NW)));
+  const rsrc_t ur0 = make_rsrc_uniform(L.U[0], L.u_bytes), ur1 = make_rsrc_uniform(L.U[1], L.u_bytes);
+  // chunk ci (path ci / nch): FI fragment and NV CK word loads per wave,
+  // whatever is in range (reads out of it give zeros)
+  auto load = [&](int ci) {
+    const int buf = ci % kBuf2;
+    const int p = ci >= nch ? 1 : 0, kb0 = (ci - p * nch) * CK;
+    const int nfr = ci < 2 * nch ? min(CK, nkb - kb0) * TT * NW : 0;
+    const uint32_t f0 = static_cast<uint32_t>((p * nkb + kb0) * TT * NW) * 1024u + lane * 16u;
 #pragma unroll
-  for (int pp = 0; pp < 2; ++pp) {
-    const rsrc_t ur = make_rsrc_uniform(pp ? L.U[1] : L.U[0], L.u_bytes);
-    const uint32_t plane = 4u * nbu * d_out;
-    for (int e0 = tid; e0 < nkb * RW; e0 += kStage * kThreads) {
-      uint32_t wv[kStage];
+    for (int i = 0; i < FI; ++i) {
+      const int f = wave + kWaves * i;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(fr, (lds_ptr)(bs(buf) + f * 64), 16,
+                                               f < nfr ? f0 + f * 1024u : kOob, 0, 0, 0);
+    }
+    const rsrc_t ur = p ? ur1 : ur0;
 #pragma unroll
-      for (int u = 0; u < kStage; ++u) {
-        const int e = e0 + u * kThreads;
-        const int kb = e / RW, row = qrow0 + (e - kb * RW);
-        const bool ok = e < nkb * RW && row < d_out;
-        const bool full = ok && kb < nbu, tl = ok && kb == nbu && tailu != 0;
-        const uint32_t toff = tailu <= 16 ? plane + 2u * row : plane + 4u * row;
-        const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(
-            ur, full ? static_cast<uint32_t>(kb * d_out + row) * 4u : kOob, 0, 0);
-        const uint32_t lo = static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(ur, tl ? toff : kOob, 0, 0));
-        const uint32_t hi = static_cast<uint16_t>(
-            __builtin_amdgcn_raw_buffer_load_b16(ur, tl && tailu > 16 ? toff + 2 : kOob, 0, 0));
-        wv[u] = w | lo | (hi << 16);
-      }
+    for (int u = 0; u < CK; ++u) {
+      const int kb = kb0 + u;
 #pragma unroll
-      for (int u = 0; u < kStage; ++u) {
-        const int e = e0 + u * kThreads;
-        if (e < nkb * RW) uwl[pp * nkb * RW + e] = wv[u];
+      for (int d = 0; d < NV; ++d) {
+        // 32-bit tail entries sit where a full word would
+        const int row = row0 + 64 * d + lane;
+        const bool on = ci < 2 * nch && (kb < nbu || (kb == nbu && tailu > 16)) && row < d_out;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ur, (lds_ptr)(us(buf, u, wave) + 64 * d), 4,
+                                                 on ? static_cast<uint32_t>(kb * d_out + row) * 4u : kOob, 0, 0, 0);
       }
     }
-  }
-  __syncthreads();
-  const rsrc_t fr = make_rsrc_uniform(L.wlat, static_cast<uint32_t>(frag_bytes(T, r, NW)));
-  const uint32_t ones[4] = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-  floatx4 yv[RB][TT];
+  };
 #pragma unroll
-  for (int pp = 0; pp < 2; ++pp) {
-    floatx4 acc[RB][TT];
+  for (int ci = 0; ci < kBuf2 - 1; ++ci) load(ci);
+  if (tail16)
+#pragma unroll
+    for (int pp = 0; pp < 2; ++pp)
+#pragma unroll
+      for (int d = 0; d < NV; ++d) {
+        const int row = row0 + 64 * d + lane;
+        ut(pp, wave)[64 * d + lane] = static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(
+            pp ? ur1 : ur0, row < d_out ? 4u * nbu * d_out + 2u * row : kOob, 0, 0));
+      }
+  uint32_t sgn_m = 0x80008000u, one_b = 0x3F803F80u;  // in registers: one VALU op per operand register
+  asm volatile("" : "+v"(sgn_m), "+v"(one_b));
+  floatx4 acc[RB][TT], yv[RB][TT];
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int j = 0; j < TT; ++j) acc[b][j] = yv[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // y += h_p acc, acc = 0 (rows row0 + 16 b + 4 gq + e)
+  auto fold = [&](int p) {
+    const rsrc_t hr = make_rsrc_uniform(p ? L.h[1] : L.h[0], L.h_bytes);
 #pragma unroll
     for (int b = 0; b < RB; ++b)
 #pragma unroll
-      for (int j = 0; j < TT; ++j) acc[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const uint32_t* ucol = uwl + pp * nkb * RW + 16 * wave + n16;
-    // byte offset of fragment (token tile j, block kb, term a) of this lane
-    const uint32_t fbase = static_cast<uint32_t>(pp * TT * nkb * NW * 64 + lane) * 16u;
-    for (int kb = 0; kb < nkb; ++kb) {
+      for (int e = 0; e < 4; ++e) {
+        const float hv = bits_to_f32<SC>(bload<SC>(hr, row0 + 16 * b + 4 * gq + e));
+#pragma unroll
+        for (int j = 0; j < TT; ++j) {
+          yv[b][j][e] += hv * acc[b][j][e];
+          acc[b][j][e] = 0.0f;
+        }
+      }
+  };
+#pragma unroll 1
+  for (int ci = 0; ci < 2 * nch; ++ci) {
+    // chunk ci has landed (each wave waits for its own loads, the barrier for
+    // everyone's) and every wave is done with the buffer of chunk ci - 1
+    wait_barrier<(kBuf2 - 2) * (FI + NV * CK)>();
+    load(ci + kBuf2 - 1);
+    if (!active) continue;
+    const int p = ci >= nch ? 1 : 0, kb0 = (ci - p * nch) * CK, buf = ci % kBuf2;
+    if (ci == nch) fold(0);
+#pragma unroll
+    for (int u = 0; u < CK; ++u) {
+      const int kb = kb0 + u;
+      if (kb >= nkb) break;
+      const uint32_t* wp = tail16 && kb == nbu ? ut(p, wave) : us(buf, u, wave);
+      uint32_t words[RB];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) words[b] = wp[16 * b + n16] >> (4 * gq);
       u32x4 B[TT][NW];
 #pragma unroll
       for (int j = 0; j < TT; ++j)
 #pragma unroll
-        for (int a = 0; a < NW; ++a)
-          B[j][a] = __builtin_amdgcn_raw_buffer_load_b128(
-              fr, fbase + static_cast<uint32_t>(((j * nkb + kb) * NW + a) * 64) * 16u, 0, 0);
+        for (int a = 0; a < NW; ++a) B[j][a] = bs(buf)[((u * TT + j) * NW + a) * 64 + lane];
 #pragma unroll
       for (int b = 0; b < RB; ++b) {
-        const u32x4 A = sign_terms(ucol[kb * RW + 16 * kWaves * b], gq, ones);
+        u32x4 A;
 #pragma unroll
-        for (int j = 0; j < TT; ++j)
+        for (int v = 0; v < 4; ++v) A[v] = ((words[b] << (15 - v)) & sgn_m) | (one_b & ~sgn_m);
 #pragma unroll
-          for (int a = 0; a < NW; ++a) acc[b][j] = mfma(A, B[j][a], acc[b][j]);
+        for (int a = 0; a < NW; ++a)
+#pragma unroll
+          for (int j = 0; j < TT; ++j) acc[b][j] = mfma(A, B[j][a], acc[b][j]);
       }
-    }
-    // y = h_0 acc_0 + h_1 acc_1 at rows qrow0 + 16 (wave + 4 b) + 4 gq + e
-    const rsrc_t hr = make_rsrc_uniform(pp ? L.h[1] : L.h[0], L.h_bytes);
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
-      float hv[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) hv[e] = bits_to_f32<SC>(bload<SC>(hr, qrow0 + 16 * (wave + kWaves * b) + 4 * gq + e));
-#pragma unroll
-      for (int j = 0; j < TT; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float v = hv[e] * acc[b][j][e];
-          yv[b][j][e] = pp == 0 ? v : yv[b][j][e] + v;
-        }
     }
   }
+  // global-to-LDS loads past the end are still in flight: none may land after
+  // the workgroup's LDS is given away
+  __builtin_amdgcn_s_waitcnt(0);
+  if (!active) return;
+  fold(1);
+  // 4 consecutive outputs per lane and token
+  const bool vec = d_out % 4 == 0 && reinterpret_cast<uintptr_t>(L.y) % (ACT == kDtF32 ? 16 : 8) == 0;
 #pragma unroll
-  for (int b = 0; b < RB; ++b)
+  for (int b = 0; b < RB; ++b) {
+    const int i = row0 + 16 * b + 4 * gq;
 #pragma unroll
-    for (int j = 0; j < TT; ++j)
+    for (int j = 0; j < TT; ++j) {
+      const int t = 16 * j + n16;
+      if (t >= T) continue;
+      const int64_t o = static_cast<int64_t>(t) * d_out + i;
+      if (vec) {
+        if (i >= d_out) continue;
+        if constexpr (ACT == kDtF32) {
+          *reinterpret_cast<floatx4*>(static_cast<float*>(L.y) + o) = yv[b][j];
+        } else {
+          uint32_t h[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = qrow0 + 16 * (wave + kWaves * b) + 4 * gq + e;
-        const int t = 16 * j + n16;
-        if (t < T && i < d_out) st<ACT>(L.y, static_cast<int64_t>(t) * d_out + i, yv[b][j][e]);
+          for (int e = 0; e < 4; ++e) h[e] = round16<ACT>(yv[b][j][e]);
+          *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(L.y) + o) =
+              u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i + e < d_out) st<ACT>(L.y, o + e, yv[b][j][e]);
       }
+    }
+  }
+}
+
+template <int TT, int ACT, int SC>
+__global__ void __launch_bounds__(kThreads) sm_s2_kernel(const uint32_t* __restrict__ hdr,
+                                                         const StreamLinear* __restrict__ descs,
+                                                         const uint32_t* __restrict__ map, uint64_t fp) {
+  if (!plan_ok(hdr, fp)) return;
+  const uint32_t code = map[blockIdx.x];
+  sm_s2_body<TT, rb_of(TT), ACT, SC>(descs[code >> 16], static_cast<int>(code & 0xffffu));
 }
 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-size_t s2_smem_bytes(int nkb, int rw) { return 4u * 2u * nkb * rw; }
-
 struct PlanLayout {
+  int bpr = kMaxBpr;
   int n1 = 0, nr = 0, n2 = 0;
-  int n1_cls[5] = {0, 0, 0, 0, 0};  // S1 items of token-tile count <= k are map entries [0, n1_cls[k])
+  int n1_cls[4 * kMtClasses + 1] = {};  // S1 items of classes < k are map entries [0, n1_cls[k])
   int n2_cls[5] = {0, 0, 0, 0, 0};  // the same for S2 items
-  int nkb_max = 1;
   size_t desc_off = 0, map1_off = 0, mapr_off = 0, map2_off = 0, data_off = 0, bytes = 0;
 };
 
+int r_groups(const ForwardArgs& a) { return (r_items(a.T, a.r) + kThreads - 1) / kThreads; }
+int s2_groups(const ForwardArgs& a) {
+  const int rw = 16 * kWaves * rb_of((a.T + 15) / 16);
+  return (a.d_out + rw - 1) / rw;
+}
+
 PlanLayout plan_layout(const ForwardArgs* a, int n) {
   PlanLayout P;
+  // the longest runs (fewest partial sums) that still give kWantWg1 workgroups
+  for (;; P.bpr /= 2) {
+    int64_t n1 = 0;
+    for (int i = 0; i < n; ++i)
+      if (has_work(a[i])) {
+        const SmGeom g = sm_geometry(a[i], P.bpr);
+        n1 += 2 * g.ng * g.s1d;
+      }
+    if (n1 >= kWantWg1 || P.bpr == kMinBpr) break;
+  }
   size_t data = 0;
   for (int i = 0; i < n; ++i) {
     if (!has_work(a[i])) continue;
-    const SmGeom g = sm_geometry(a[i]);
-    const int rw = rw_of(g.tt);
-    P.nkb_max = std::max(P.nkb_max, nblocks32(a[i].r));
+    const SmGeom g = sm_geometry(a[i], P.bpr);
     P.n1 += 2 * g.ng * g.s1d;
-    P.n1_cls[g.tt] += 2 * g.ng * g.s1d;
-    const int nr = static_cast<int>((2 * 16 * g.tt * 32 * nblocks32(a[i].r) + kThreads - 1) / kThreads);
-    P.nr += nr;
-    P.n2 += (a[i].d_out + rw - 1) / rw;
-    P.n2_cls[g.tt] += (a[i].d_out + rw - 1) / rw;
-    data += align256(sizeof(float) * 2 * a[i].T * g.s1d * a[i].r) +
-            align256(frag_bytes(a[i].T, a[i].r, nw_of(a[i].act_dt)));
+    P.n1_cls[g.cls + 1] += 2 * g.ng * g.s1d;
+    P.nr += r_groups(a[i]);
+    P.n2 += s2_groups(a[i]);
+    P.n2_cls[g.tt] += s2_groups(a[i]);
+    data += align256(part_bytes(g)) + align256(frag_bytes(a[i].T, a[i].r, nw_of(a[i].act_dt)));
   }
-  for (int k = 1; k < 5; ++k) {
-    P.n1_cls[k] += P.n1_cls[k - 1];
-    P.n2_cls[k] += P.n2_cls[k - 1];
-  }
+  for (int k = 1; k <= 4 * kMtClasses; ++k) P.n1_cls[k] += P.n1_cls[k - 1];
+  for (int k = 1; k < 5; ++k) P.n2_cls[k] += P.n2_cls[k - 1];
   P.desc_off = kCtrlBytes;
   P.map1_off = P.desc_off + align256(sizeof(StreamLinear) * static_cast<size_t>(n));
   P.mapr_off = P.map1_off + align256(4 * static_cast<size_t>(P.n1));
@@ -460,24 +643,29 @@ PlanLayout plan_layout(const ForwardArgs* a, int n) {
   return P;
 }
 
+template <int TT, int C, int ACT, int SC>
+void launch_s1(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stream) {
+  constexpr int MT = mt_cls(TT, C), k = (TT - 1) * kMtClasses + C;
+  const int n = P.n1_cls[k + 1] - P.n1_cls[k];
+  if (n == 0) return;
+  hipLaunchKernelGGL((sm_s1_kernel<TT, MT, ACT, SC>), dim3(n), dim3(kThreads), (S1Lds<TT, MT, ACT, SC>::kBytes),
+                     stream, reinterpret_cast<const uint32_t*>(b),
+                     reinterpret_cast<const StreamLinear*>(b + P.desc_off),
+                     reinterpret_cast<const uint32_t*>(b + P.map1_off) + P.n1_cls[k], fp);
+}
 template <int TT, int ACT, int SC>
 void launch_s1(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stream) {
-  const int n = P.n1_cls[TT] - P.n1_cls[TT - 1];
-  if (n == 0) return;
-  hipLaunchKernelGGL((sm_s1_kernel<TT, mt_of(TT), ACT, SC>), dim3(n), dim3(kThreads), 0, stream,
-                     reinterpret_cast<const uint32_t*>(b), reinterpret_cast<const StreamLinear*>(b + P.desc_off),
-                     reinterpret_cast<const uint32_t*>(b + P.map1_off) + P.n1_cls[TT - 1], fp);
+  launch_s1<TT, 0, ACT, SC>(b, P, fp, stream);
+  launch_s1<TT, 1, ACT, SC>(b, P, fp, stream);
+  launch_s1<TT, 2, ACT, SC>(b, P, fp, stream);
+  launch_s1<TT, 3, ACT, SC>(b, P, fp, stream);
 }
 
 template <int TT, int ACT, int SC>
 void launch_s2(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stream) {
   const int n = P.n2_cls[TT] - P.n2_cls[TT - 1];
   if (n == 0) return;
-  const size_t smem = s2_smem_bytes(P.nkb_max, rw_of(TT));
-  if (smem > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&sm_s2_kernel<TT, ACT, SC>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
-  hipLaunchKernelGGL((sm_s2_kernel<TT, ACT, SC>), dim3(n), dim3(kThreads), smem, stream,
+  hipLaunchKernelGGL((sm_s2_kernel<TT, ACT, SC>), dim3(n), dim3(kThreads), (S2Lds<TT, rb_of(TT), ACT>::kBytes), stream,
                      reinterpret_cast<const uint32_t*>(b), reinterpret_cast<const StreamLinear*>(b + P.desc_off),
                      reinterpret_cast<const uint32_t*>(b + P.map2_off) + P.n2_cls[TT - 1], fp);
 }
@@ -489,7 +677,7 @@ void launch_all(const void* ws, const PlanLayout& P, uint64_t fp, hipStream_t st
   launch_s1<2, ACT, SC>(b, P, fp, stream);
   launch_s1<3, ACT, SC>(b, P, fp, stream);
   launch_s1<4, ACT, SC>(b, P, fp, stream);
-  hipLaunchKernelGGL((sm_r_kernel<nw_of(ACT)>), dim3(P.nr), dim3(kThreads), 0, stream,
+  hipLaunchKernelGGL((sm_r_kernel<nw_of(ACT), SC>), dim3(P.nr), dim3(kThreads), 0, stream,
                      reinterpret_cast<const uint32_t*>(b), reinterpret_cast<const StreamLinear*>(b + P.desc_off),
                      reinterpret_cast<const uint32_t*>(b + P.mapr_off), fp);
   launch_s2<1, ACT, SC>(b, P, fp, stream);
@@ -522,10 +710,11 @@ bool stream_mma_supports(const ForwardArgs& a) {
   const int64_t rows = 16 * ((a.T + 15) / 16);
   if ((rows + 1) * a.d_in * ex >= lim || packed_bytes64(a.d_out, a.r) >= lim || packed_bytes64(a.r, a.d_in) >= lim)
     return false;
-  const SmGeom g = sm_geometry(a);
-  if (g.s1d > kMaxRuns || g.ng > kMaxGroups) return false;
+  // at most kMaxRuns runs of 16, 32 or 64 blocks (by token tiles)
+  const int tt = (a.T + 15) / 16;
+  if (nblocks32(a.d_in) > kMaxRuns * (tt == 1 ? 16 : (tt == 2 ? 32 : 64))) return false;
   // map codes: 16 bits of work index per linear
-  if (2 * 16 * g.tt * 32 * nblocks32(a.r) > 65535 * kThreads || a.d_out > 65535 * 64) return false;
+  if (2 * 16 * tt * 32 * nblocks32(a.r) > 65535 * kThreads || a.d_out > 65535 * 64) return false;
   return true;
 }
 
@@ -546,7 +735,8 @@ hipError_t stream_mma_init(const ForwardArgs* a, int n, uint64_t fp, void* ws, h
   uint32_t* mr = reinterpret_cast<uint32_t*>(host.data() + P.mapr_off);
   uint32_t* m2 = reinterpret_cast<uint32_t*>(host.data() + P.map2_off);
   char* data = static_cast<char*>(ws) + P.data_off;
-  int i1[4] = {P.n1_cls[0], P.n1_cls[1], P.n1_cls[2], P.n1_cls[3]}, ir = 0;
+  int i1[4 * kMtClasses], ir = 0;
+  std::copy(P.n1_cls, P.n1_cls + 4 * kMtClasses, i1);
   int i2[4] = {P.n2_cls[0], P.n2_cls[1], P.n2_cls[2], P.n2_cls[3]};
   for (int i = 0; i < n; ++i) {
     StreamLinear& L = D[i];
@@ -565,9 +755,10 @@ hipError_t stream_mma_init(const ForwardArgs* a, int n, uint64_t fp, void* ws, h
     L.d_out = f.d_out;
     L.r = f.r;
     if (!has_work(f)) continue;
-    const SmGeom g = sm_geometry(f);
+    const SmGeom g = sm_geometry(f, P.bpr);
     L.s1d = g.s1d;
     L.bpr = g.bpr;
+    L.mt = g.mt;
     const int64_t ex = f.act_dt == kDtF32 ? 4 : 2, es = f.sc_dt == kDtF32 ? 4 : 2;
     L.x_bytes = static_cast<uint32_t>(static_cast<int64_t>(f.T) * f.d_in * ex);
     L.g_bytes = static_cast<uint32_t>(f.d_in * es);
@@ -576,18 +767,17 @@ hipError_t stream_mma_init(const ForwardArgs* a, int n, uint64_t fp, void* ws, h
     L.v_bytes = static_cast<uint32_t>(packed_bytes64(f.r, f.d_in));
     L.u_bytes = static_cast<uint32_t>(packed_bytes64(f.d_out, f.r));
     L.part = reinterpret_cast<float*>(data);
-    data += align256(sizeof(float) * 2 * f.T * g.s1d * f.r);
+    data += align256(part_bytes(g));
     L.wlat = reinterpret_cast<float*>(data);  // the B fragments of stage 2
     data += align256(frag_bytes(f.T, f.r, nw_of(f.act_dt)));
-    // S1 and S2 items grouped by token-tile count (one launch each)
+    // S1 items grouped by class, S2 items by token-tile count (one launch each)
     for (int p = 0; p < 2; ++p)
       for (int gr = 0; gr < g.ng; ++gr)
         for (int c = 0; c < g.s1d; ++c)
-          m1[i1[g.tt - 1]++] = (static_cast<uint32_t>(i) << 16) | (p << 15) | (gr << 9) | c;
-    const int nrb = (2 * 16 * g.tt * 32 * nblocks32(f.r) + kThreads - 1) / kThreads;
+          m1[i1[g.cls]++] = (static_cast<uint32_t>(i) << 16) | (p << 15) | (gr << 9) | c;
+    const int nrb = r_groups(f);
     for (int j = 0; j < nrb; ++j) mr[ir++] = (static_cast<uint32_t>(i) << 16) | j;
-    const int rw = rw_of(g.tt);
-    const int nrow = (f.d_out + rw - 1) / rw;
+    const int nrow = s2_groups(f);
     for (int j = 0; j < nrow; ++j) m2[i2[g.tt - 1]++] = (static_cast<uint32_t>(i) << 16) | j;
   }
   hipError_t e = hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, stream);

@@ -18,10 +18,11 @@ struct alignas(16) StreamLinear {
   const void* h[2];
   const void* g[2];
   const void* l[2];
-  float* part;  // [2][T][s1d][r] partial sums l (.) z of each run
-  float* wlat;  // [2][T][r]      w = l (.) z
+  float* part;  // partial sums of each run: [2][T][s1d][r] of l (.) z, or z in accumulator order (matrix cores)
+  float* wlat;  // w = l (.) z: [2][T][r], or stage 2's B fragments
   int T, d_in, d_out, r;
   int s1d, bpr;
+  int mt;  // matrix-core stage 1: latent tiles per wave
   uint32_t x_bytes, g_bytes, h_bytes, l_bytes, v_bytes, u_bytes;
 };
 

@@ -240,3 +240,26 @@ def test_mma_list_plan_mismatch_and_graph_replays():
         for i in range(len(lins)):
             assert _same_bits(ys[i], y_eager[i]), (rep, i)
     assert lb.lb_workspace_status(L.workspace) == 0
+
+
+# (T, d_in, d_out, r): ranks at the edges of the 2-, 3-, 5- and 6-or-8-tile classes of a wave and of one and two
+# groups of them; output rows around the 256- and 512-row workgroups; tails of d_in of 4, 12, 20 and 28 inputs (rows that
+# are and are not whole 16-byte pieces); runs of one block, of a chunk and of several
+EDGE_MMA = [(3, 36, 511, 128), (16, 100, 513, 129), (9, 2588, 64, 192), (4, 1000, 36, 193), (16, 268, 20, 320),
+            (7, 524, 257, 321), (12, 96, 1, 512), (5, 4092, 40, 513), (32, 316, 255, 384), (17, 64, 256, 640),
+            (48, 200, 130, 289), (33, 44, 300, 385), (64, 2060, 257, 577), (49, 24, 12, 1024)]
+
+
+@pytest.mark.parametrize("act,sc", [("bf16", "f16"), ("f32", "f16"), ("f16", "f32"), ("f32", "bf16")])
+def test_mma_list_tile_edges(act, sc):
+    lins = _linears(EDGE_MMA, cfg=45, act=act, sc=sc)
+    L, ys = _run_list(lins)
+    first = [y.clone() for y in ys]
+    for i, ((li, _, _), y) in enumerate(zip(lins, ys)):
+        _check(li, U.torch_to_raw(y, act), label=f"mma list {EDGE_MMA[i]} {act}/{sc}")
+    # the loads run ahead of their use: a second pass over other buffer contents gives the same bits
+    for y in ys:
+        y.zero_()
+    L.forward()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(first, ys))
