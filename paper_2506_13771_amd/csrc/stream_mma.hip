@@ -115,8 +115,8 @@ __device__ __forceinline__ void wait_barrier() {
 // are cut once per workgroup (a wave that cut its own spent 40 instructions a
 // block on them), partial sums leave as 16-byte stores, and the waves split the
 // latents, not the blocks, so no sum crosses waves.
-constexpr int kBuf1 = 4;
-__host__ __device__ constexpr int cb_of(int tt) { return tt <= 2 ? 2 : 1; }
+constexpr int kBuf1 = 3;
+__host__ __device__ constexpr int cb_of(int tt, int act) { return tt >= 3 && act == kDtF32 ? 1 : 2; }
 
 // LDS of S1: the run's g terms, the x and V-word buffers, the tail block's
 // words.  One array: of several the compiler would follow each buffer's loads
@@ -124,12 +124,13 @@ __host__ __device__ constexpr int cb_of(int tt) { return tt <= 2 ? 2 : 1; }
 template <int TT, int MT, int ACT, int SC>
 struct S1Lds {
   static constexpr int XC = ACT == kDtF32 ? 2 : 1;
-  static constexpr int XI = (cb_of(TT) * TT * XC + kWaves - 1) / kWaves;
+  static constexpr int CB = cb_of(TT, ACT);
+  static constexpr int XI = (CB * TT * XC + kWaves - 1) / kWaves;  // x fragments per wave and chunk
   static constexpr int NV = (MT + 3) / 4;
-  static constexpr int kXbuf = XI * kWaves * 1024;
+  static constexpr int kXbuf = (TT == 1 ? CB * XC : XI * kWaves) * 1024;
   static constexpr int kXs = kMaxBpr * 4 * nterms<SC>() * 16;
   static constexpr int kVs = kXs + kBuf1 * kXbuf;
-  static constexpr int kVt = kVs + kBuf1 * cb_of(TT) * kWaves * NV * 256;
+  static constexpr int kVt = kVs + kBuf1 * CB * kWaves * NV * 256;
   static constexpr int kBytes = kVt + kWaves * NV * 256;
   static_assert(kBytes <= 65536, "no launch attribute needed");
 };
@@ -138,7 +139,7 @@ template <int TT, int MT, int ACT, int SC>
 __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp, int c) {
   constexpr int NG = nterms<SC>(), NX = nterms<ACT>();
   constexpr int EX = ACT == kDtF32 ? 4 : 2;
-  constexpr int CB = cb_of(TT);
+  constexpr int CB = cb_of(TT, ACT);
   constexpr int XC = EX / 2;                       // 16-byte pieces of a lane's 8 inputs
   constexpr int kXf = CB * TT * XC;                  // x fragments (1 KB) of a chunk
   constexpr int XI = (kXf + kWaves - 1) / kWaves;    // of them per wave
@@ -168,50 +169,53 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
   const bool xv = d_in % (16 / EX) == 0 && reinterpret_cast<uintptr_t>(L.x) % 16 == 0;
   const bool tail16 = tailv != 0 && tailv <= 16 && b1 > nbv;  // 16-bit tail words
 
-  // loads of chunk ch into its buffer: every wave issues XI x loads (4 times
-  // as many, of 4 bytes a lane, when rows are not whole 16-byte pieces) and
-  // NV CB word loads, whatever is in range (reads out of it give zeros, so x is
-  // zero past d_in and past T)
-  auto load = [&](int ch) {
-    const int buf = ch % kBuf1, bb = b0 + ch * CB;
+  // loads of chunk ch into its buffer: x fragments as 16-byte pieces of rows
+  // (4-byte ones when rows are not whole pieces; up to 16 tokens always, each
+  // wave a quarter of every fragment) and NV CB word loads per wave.  x is zero
+  // past d_in and past T; words past r or past the run are whatever is there
+  // (zero past the buffer): no product of theirs is kept.
+  const uint32_t xlane = static_cast<uint32_t>(n16) * d_in + 8 * gq;
+  auto load_x4 = [&](char* dst, int tt, int j, int d, bool on) {
+    // dword lane + 64 d of the fragment: lane (lane + 64 d) / 4 of the 16-byte form, dword % 4 of its piece
+    const int ln = (lane >> 2) + 16 * d;
+    const int e = j + 8 * (ln >> 4) + (lane & 3) * (4 / EX);
+    const uint32_t off = (static_cast<uint32_t>(16 * tt + (ln & 15)) * d_in + e) * EX;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_ptr)(dst + 256 * d), 4, on && e < d_in ? off : kOob, 0, 0, 0);
+  };
+  const uint32_t vlane = 16 * t0 + lane;
+  auto load = [&](int ch, int buf) {
+    const int bb = b0 + ch * CB;
+    if constexpr (TT == 1) {
 #pragma unroll
-    for (int i = 0; i < XI; ++i) {
-      const int f = wave + kWaves * i;  // (block, token tile, piece), piece fastest
-      const int pc = f % XC, tt = (f / XC) % TT, bl = f / (XC * TT);
-      const bool on = f < kXf && bb + bl < b1;
-      char* dst = reinterpret_cast<char*>(xs(buf) + f * 64);
-      const int j = 32 * (bb + bl) + (4 / XC) * 2 * pc;  // piece pc of lane group gq: inputs j + 8 gq ..
-      if (xv) {
-        const uint32_t off = (static_cast<uint32_t>(16 * tt + n16) * d_in + j + 8 * gq) * EX;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            xr, (lds_ptr)dst, 16, on && 16 * tt + n16 < T && j + 8 * gq < d_in ? off : kOob, 0, 0, 0);
-      } else {
+      for (int f = 0; f < CB * XC; ++f)
+        load_x4(reinterpret_cast<char*>(xs(buf) + f * 64), 0, 32 * (bb + f / XC) + 4 * (f % XC), wave, true);
+    } else {
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          // dword lane + 64 d of the fragment: lane (lane + 64 d) / 4 of the 16-byte form, dword % 4 of its piece
-          const int ln = (lane >> 2) + 16 * d;
-          const int row = 16 * tt + (ln & 15), e = j + 8 * (ln >> 4) + (lane & 3) * (4 / EX);
-          const uint32_t off = (static_cast<uint32_t>(row) * d_in + e) * EX;
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_ptr)(dst + 256 * d), 4,
-                                                   on && row < T && e < d_in ? off : kOob, 0, 0, 0);
+      for (int i = 0; i < XI; ++i) {
+        const int f = wave + kWaves * i;  // (block, token tile, piece), piece fastest
+        const int pc = f % XC, tt = (f / XC) % TT, bl = f / (XC * TT);
+        char* dst = reinterpret_cast<char*>(xs(buf) + f * 64);
+        const int j = 32 * (bb + bl) + 4 * pc;  // piece pc of lane group gq: inputs j + 8 gq ..
+        if (xv) {
+          const uint32_t off = (static_cast<uint32_t>(16 * tt) * d_in + j + xlane) * EX;
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_ptr)dst, 16, f < kXf && j + 8 * gq < d_in ? off : kOob, 0,
+                                                   0, 0);
+        } else {
+#pragma unroll
+          for (int d = 0; d < 4; ++d) load_x4(dst, tt, j, d, f < kXf);
         }
       }
     }
 #pragma unroll
-    for (int bl = 0; bl < CB; ++bl) {
-      const int b = bb + bl;
+    for (int bl = 0; bl < CB; ++bl)
 #pragma unroll
-      for (int d = 0; d < NV; ++d) {
-        // 32-bit tail entries sit where a full word would
-        const int k = 16 * t0 + 64 * d + lane;
-        const bool on = b < b1 && (b < nbv || tailv > 16) && k < r;
+      for (int d = 0; d < NV; ++d)
+        // (32-bit tail entries sit where a full word would)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_ptr)(vs(buf, bl, wave) + 64 * d), 4,
-                                                 on ? static_cast<uint32_t>(b * r + k) * 4u : kOob, 0, 0, 0);
-      }
-    }
+                                                 (static_cast<uint32_t>(bb + bl) * r + vlane + 64 * d) * 4u, 0, 0, 0);
   };
 #pragma unroll
-  for (int ch = 0; ch < kBuf1 - 1; ++ch) load(ch);
+  for (int ch = 0; ch < kBuf1 - 1; ++ch) load(ch, ch);
 
   if (tail16)
 #pragma unroll
@@ -304,20 +308,25 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
     }
   };
   constexpr int kAhead = kBuf1 - 2;  // chunks still in flight when one is used
+  int buf = 0;
   for (int ch = 0; ch < nch; ++ch) {
     // chunk ch has landed (each wave waits for its own loads, the barrier for
     // everyone's) and every wave is done with the buffer of chunk ch - 1
-    if (xv)
+    if (TT == 1)
+      wait_barrier<kAhead * CB * (XC + NV)>();
+    else if (xv)
       wait_barrier<kAhead * (XI + CB * NV)>();
     else
       wait_barrier<kAhead * (4 * XI + CB * NV)>();
-    load(ch + kBuf1 - 1);
-    if (mts <= 0) continue;
+    load(ch + kBuf1 - 1, buf == 0 ? kBuf1 - 1 : buf - 1);
+    if (mts > 0) {
 #pragma unroll
-    for (int bl = 0; bl < CB; ++bl) {
-      const int b = b0 + ch * CB + bl;
-      if (b < b1) block(b, ch % kBuf1, bl);
+      for (int bl = 0; bl < CB; ++bl) {
+        const int b = b0 + ch * CB + bl;
+        if (b < b1) block(b, buf, bl);
+      }
     }
+    buf = buf == kBuf1 - 1 ? 0 : buf + 1;
   }
   // global-to-LDS loads past the run are still in flight: none may land after
   // the workgroup's LDS is given away
@@ -454,35 +463,29 @@ __device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
   const bool tail16 = tailu != 0 && tailu <= 16;
   const rsrc_t fr = make_rsrc_uniform(L.wlat, static_cast<uint32_t>(frag_bytes(T, r, NW)));
   const rsrc_t ur0 = make_rsrc_uniform(L.U[0], L.u_bytes), ur1 = make_rsrc_uniform(L.U[1], L.u_bytes);
-  // chunk ci (path ci / nch): FI fragment and NV CK word loads per wave,
-  // whatever is in range (reads out of it give zeros)
-  auto load = [&](int ci) {
-    const int buf = ci % kBuf2;
+  // chunk ci (path ci / nch): FI fragment and NV CK word loads per wave.
+  // Fragments past a path's blocks and words past a block's rows are whatever
+  // is there (zero past the buffers): no product of theirs is kept.
+  const uint32_t flane = wave * 1024u + lane * 16u, ulane = row0 + lane;
+  auto load = [&](int ci, int buf) {
     const int p = ci >= nch ? 1 : 0, kb0 = (ci - p * nch) * CK;
-    const int nfr = ci < 2 * nch ? min(CK, nkb - kb0) * TT * NW : 0;
-    const uint32_t f0 = static_cast<uint32_t>((p * nkb + kb0) * TT * NW) * 1024u + lane * 16u;
+    const uint32_t f0 = static_cast<uint32_t>((p * nkb + kb0) * TT * NW) * 1024u + flane;
 #pragma unroll
-    for (int i = 0; i < FI; ++i) {
-      const int f = wave + kWaves * i;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(fr, (lds_ptr)(bs(buf) + f * 64), 16,
-                                               f < nfr ? f0 + f * 1024u : kOob, 0, 0, 0);
-    }
+    for (int i = 0; i < FI; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(fr, (lds_ptr)(bs(buf) + (wave + kWaves * i) * 64), 16,
+                                               f0 + kWaves * i * 1024u, 0, 0, 0);
     const rsrc_t ur = p ? ur1 : ur0;
 #pragma unroll
-    for (int u = 0; u < CK; ++u) {
-      const int kb = kb0 + u;
+    for (int u = 0; u < CK; ++u)
 #pragma unroll
-      for (int d = 0; d < NV; ++d) {
-        // 32-bit tail entries sit where a full word would
-        const int row = row0 + 64 * d + lane;
-        const bool on = ci < 2 * nch && (kb < nbu || (kb == nbu && tailu > 16)) && row < d_out;
+      for (int d = 0; d < NV; ++d)
+        // (32-bit tail entries sit where a full word would)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ur, (lds_ptr)(us(buf, u, wave) + 64 * d), 4,
-                                                 on ? static_cast<uint32_t>(kb * d_out + row) * 4u : kOob, 0, 0, 0);
-      }
-    }
+                                                 (static_cast<uint32_t>(kb0 + u) * d_out + ulane + 64 * d) * 4u, 0, 0,
+                                                 0);
   };
 #pragma unroll
-  for (int ci = 0; ci < kBuf2 - 1; ++ci) load(ci);
+  for (int ci = 0; ci < kBuf2 - 1; ++ci) load(ci, ci);
   if (tail16)
 #pragma unroll
     for (int pp = 0; pp < 2; ++pp)
@@ -514,14 +517,15 @@ __device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
         }
       }
   };
+  int buf = 0;
 #pragma unroll 1
-  for (int ci = 0; ci < 2 * nch; ++ci) {
+  for (int ci = 0; ci < 2 * nch; ++ci, buf = buf == kBuf2 - 1 ? 0 : buf + 1) {
     // chunk ci has landed (each wave waits for its own loads, the barrier for
     // everyone's) and every wave is done with the buffer of chunk ci - 1
     wait_barrier<(kBuf2 - 2) * (FI + NV * CK)>();
-    load(ci + kBuf2 - 1);
+    load(ci + kBuf2 - 1, buf == 0 ? kBuf2 - 1 : buf - 1);
     if (!active) continue;
-    const int p = ci >= nch ? 1 : 0, kb0 = (ci - p * nch) * CK, buf = ci % kBuf2;
+    const int p = ci >= nch ? 1 : 0, kb0 = (ci - p * nch) * CK;
     if (ci == nch) fold(0);
 #pragma unroll
     for (int u = 0; u < CK; ++u) {
