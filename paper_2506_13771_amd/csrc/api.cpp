@@ -118,6 +118,20 @@ lb_kernel auto_kernel(int64_t T, int64_t d_in, int64_t d_out, int64_t r) {
   return pf ? LB_KERNEL_PREFILL : LB_KERNEL_AUTO;
 }
 
+// Whether AUTO runs the three few-token stages (launch_few_tokens) for a,
+// which a kernel above takes, instead of it.  They need the aligned groups of
+// four of the matrix-core lists.  Against the kernel above, us per call on the
+// 7B, 13B and 70B shapes: 16 tokens 12-21 (17-42 matrix-core decode), 32 tokens
+// 12-24 (15-45 prefill), 64 tokens 14-32 (15-50), except past 48 tokens with
+// very many outputs, where prefill's larger output units win (8192 -> 28672, r =
+// 304: 28.4 against 27.5).  Below 16 tokens the single-launch kernels stay,
+// which a list of calls batches, unless prefill would run (r d_out >= 8e6).
+bool prefer_few(const lb::ForwardArgs& a) {
+  if (a.T <= kAutoLutTokens || a.T > 64 || (a.T > 48 && a.d_out > 16384)) return false;
+  if (a.T < 16 && !prefer_prefill(a.T, a.d_out, a.r)) return false;
+  return lb::few_tokens_supports(a, lb_forward_workspace_bytes(a.T, a.d_in, a.d_out, a.r));
+}
+
 }  // namespace
 
 extern "C" {
@@ -252,6 +266,10 @@ lb_status lb_linear_forward_kernel(const void* x, lb_dtype act_dtype, int64_t T,
     // three on the matrix-core decode kernel, then the prefill kernels
     kernel = auto_kernel(T, d_in, d_out, r);
     if (kernel == LB_KERNEL_AUTO) return LB_ERR_SHAPE;
+    if (prefer_few(a)) {
+      e = lb::launch_few_tokens(&a, &need, 1, stream);
+      return e == hipSuccess ? LB_OK : LB_ERR_HIP;
+    }
   }
   if (kernel == LB_KERNEL_DECODE)
     e = lb::launch_decode(a, lb::decode_geometry(a.T, a.d_in, a.d_out, a.r), stream);
@@ -360,8 +378,14 @@ bool auto_unsupported(const lb_linear_desc& d) {
   return has_work(d) && auto_kernel(d.T, d.d_in, d.d_out, d.r) == LB_KERNEL_AUTO;
 }
 
-// the list launch a linear joins: the look-up-table or the matrix-core decode
-// kernel (what AUTO runs for it), or none (a call of its own)
+// a linear AUTO runs by the few-token stages
+bool runs_few(const lb_linear_desc& d) {
+  return has_work(d) && auto_kernel(d.T, d.d_in, d.d_out, d.r) != LB_KERNEL_AUTO &&
+         prefer_few(make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, nullptr, 0));
+}
+
+// the list launch another linear joins: the look-up-table or the matrix-core
+// decode kernel (what AUTO runs for it), or none (a call of its own)
 lb_kernel list_kernel(const lb_linear_desc& d) {
   if (!has_work(d)) return LB_KERNEL_AUTO;
   const lb_kernel k = auto_kernel(d.T, d.d_in, d.d_out, d.r);
@@ -439,13 +463,35 @@ lb_status lb_linear_forward_many(const lb_linear_desc* descs, int64_t n, void* w
     nb = 0;
     return e == hipSuccess ? LB_OK : LB_ERR_HIP;
   };
+  // linears of the few-token stages, by token tiles: up to kFewMaxBatch of one
+  // pair of dtypes to a launch of each stage (nothing depends on their order)
+  struct FewBatch {
+    lb::ForwardArgs a[lb::kFewMaxBatch];
+    size_t bytes[lb::kFewMaxBatch];
+    int n = 0;
+  } few[4];
+  auto flush_few = [&](FewBatch& f) -> lb_status {
+    if (f.n == 0) return LB_OK;
+    const hipError_t e = lb::launch_few_tokens(f.a, f.bytes, f.n, stream);
+    f.n = 0;
+    return e == hipSuccess ? LB_OK : LB_ERR_HIP;
+  };
   char* ws = static_cast<char*>(workspace);
   size_t off = lb::kListHdrBytes;
   for (int64_t i = 0; i < n; ++i) {
     const lb_linear_desc& d = descs[i];
     const size_t sb = slice_bytes(d);
     const lb_kernel k = list_kernel(d);
-    if (k != LB_KERNEL_AUTO) {
+    if (runs_few(d)) {
+      FewBatch& f = few[(d.T + 15) / 16 - 1];
+      if (f.n > 0 && (f.n == lb::kFewMaxBatch || static_cast<int>(d.act_dtype) != f.a[0].act_dt ||
+                      static_cast<int>(d.scale_dtype) != f.a[0].sc_dt)) {
+        const lb_status st = flush_few(f);
+        if (st != LB_OK) return st;
+      }
+      f.a[f.n] = make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, ws + off, sb);
+      f.bytes[f.n++] = lb_forward_workspace_bytes(d.T, d.d_in, d.d_out, d.r);
+    } else if (k != LB_KERNEL_AUTO) {
       if (nb > 0 && (nb == lb::kDecodeMaxBatch || k != bk || static_cast<int>(d.act_dtype) != batch[0].act_dt ||
                      static_cast<int>(d.scale_dtype) != batch[0].sc_dt)) {
         const lb_status st = flush();
@@ -461,6 +507,10 @@ lb_status lb_linear_forward_many(const lb_linear_desc* descs, int64_t n, void* w
       if (st != LB_OK) return st;
     }
     off += sb;
+  }
+  for (FewBatch& f : few) {
+    const lb_status st = flush_few(f);
+    if (st != LB_OK) return st;
   }
   return flush();
 }

@@ -24,6 +24,7 @@
 // Inputs of this path: x and g read as aligned groups of four (d_in a
 // multiple of 4, x and g aligned to four elements).
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <vector>
 
@@ -45,6 +46,7 @@ using splan::StreamLinear;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = 4;
+constexpr int kGroups = 4;  // one linear: groups of 4 waves taking turns over the blocks of a reduction
 constexpr int kMaxTok = 64;
 constexpr int kMaxRank = 1024;
 constexpr int kMaxRuns = 511;   // S1 map code: 9 bits of run
@@ -106,8 +108,8 @@ __device__ __forceinline__ void wait_barrier() {
 }
 
 // Wave w of a group holds latent tiles t0 + (0 .. mt - 1), t0 = (4 grp + w) mt.
-// x (shared by the waves) and each wave's V words stream through kBuf1 LDS
-// buffers of CB blocks, filled by global-to-LDS loads kBuf1 - 1 chunks ahead:
+// x (shared by the waves) and each wave's V words stream through a ring of
+// LDS buffers of CB blocks, filled by global-to-LDS loads kBuf - 1 chunks ahead:
 // loads into registers had cost the occupancy that was to hide their latency.
 // What bounds it then: building the A operands, 13 VALU instructions per tile
 // and block with f16 scales (2 terms) for 2 matrix instructions per token tile,
@@ -115,36 +117,51 @@ __device__ __forceinline__ void wait_barrier() {
 // are cut once per workgroup (a wave that cut its own spent 40 instructions a
 // block on them), partial sums leave as 16-byte stores, and the waves split the
 // latents, not the blocks, so no sum crosses waves.
-constexpr int kBuf1 = 3;
+constexpr int kBuf1 = 3;         // lists: several workgroups a CU hide the rest of the latency
+constexpr size_t kOneLds = 150 * 1024;  // one linear: about one workgroup a CU, so as deep as its LDS goes
+constexpr int kOneBuf = 8;
 __host__ __device__ constexpr int cb_of(int tt, int act) { return tt >= 3 && act == kDtF32 ? 1 : 2; }
 
 // LDS of S1: the run's g terms, the x and V-word buffers, the tail block's
 // words.  One array: of several the compiler would follow each buffer's loads
 // and wait for the newest before every read.
-template <int TT, int MT, int ACT, int SC>
+template <int TT, int MT, int ACT, int SC, bool ONE = false>
 struct S1Lds {
   static constexpr int XC = ACT == kDtF32 ? 2 : 1;
-  static constexpr int CB = cb_of(TT, ACT);
-  static constexpr int XI = (CB * TT * XC + kWaves - 1) / kWaves;  // x fragments per wave and chunk
+  static constexpr int G = ONE ? kGroups : 1, NWV = G * kWaves;  // wave groups, waves
+  static constexpr int CB = ONE ? G : cb_of(TT, ACT);
+  static constexpr int XI = (CB * TT * XC + NWV - 1) / NWV;  // x fragments per wave and chunk
   static constexpr int NV = (MT + 3) / 4;
-  static constexpr int kXbuf = (TT == 1 ? CB * XC : XI * kWaves) * 1024;
+  static constexpr int kXbuf = (TT == 1 ? CB * XC : XI * NWV) * 1024;
   static constexpr int kXs = kMaxBpr * 4 * nterms<SC>() * 16;
-  static constexpr int kVs = kXs + kBuf1 * kXbuf;
-  static constexpr int kVt = kVs + kBuf1 * CB * kWaves * NV * 256;
-  static constexpr int kBytes = kVt + kWaves * NV * 256;
-  static_assert(kBytes <= 65536, "no launch attribute needed");
+  static constexpr int kVbuf = CB * kWaves * NV * 256;
+  // most vector-memory operations of a wave per chunk, of at most 63 in flight
+  static constexpr int kXops = TT == 1 ? CB * XC / G : 4 * XI, kVops = CB / G * NV;
+  static constexpr int kOps = kXops + kVops;
+  static constexpr int kDeep = static_cast<int>((kOneLds - kXs) / (kXbuf + kVbuf));
+  static constexpr int kDeepOps = 2 + 63 / kOps;
+  static constexpr int kBuf =
+      !ONE ? kBuf1
+           : (kDeep < kOneBuf ? (kDeep < kDeepOps ? kDeep : kDeepOps) : (kOneBuf < kDeepOps ? kOneBuf : kDeepOps));
+  static constexpr int kVs = kXs + kBuf * kXbuf;
+  static constexpr int kVt = kVs + kBuf * kVbuf;
+  static constexpr int kRed = 2 * kWaves * MT * TT * 1024;  // ONE: two groups' sums, in place of the ring
+  static constexpr int kRing = kVt + NWV * NV * 256;
+  static constexpr int kBytes = ONE && kRed > kRing ? kRed : kRing;
+  static_assert(kBuf >= 2 && kBytes <= (ONE ? 160 * 1024 : 65536), "ring depth; no launch attribute for lists");
 };
 
-template <int TT, int MT, int ACT, int SC>
+template <int TT, int MT, int ACT, int SC, bool ONE>
 __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp, int c) {
   constexpr int NG = nterms<SC>(), NX = nterms<ACT>();
   constexpr int EX = ACT == kDtF32 ? 4 : 2;
-  constexpr int CB = cb_of(TT, ACT);
+  constexpr int CB = ONE ? kGroups : cb_of(TT, ACT);
   constexpr int XC = EX / 2;                       // 16-byte pieces of a lane's 8 inputs
   constexpr int kXf = CB * TT * XC;                  // x fragments (1 KB) of a chunk
-  constexpr int XI = (kXf + kWaves - 1) / kWaves;    // of them per wave
+  constexpr int XI = S1Lds<TT, MT, ACT, SC, ONE>::XI;  // of them per wave
   constexpr int NV = (MT + 3) / 4;                   // word loads (64 latents) per wave and block
-  using Lds = S1Lds<TT, MT, ACT, SC>;
+  using Lds = S1Lds<TT, MT, ACT, SC, ONE>;
+  constexpr int kBuf = Lds::kBuf, G = Lds::G, NWV = Lds::NWV;
   extern __shared__ __attribute__((aligned(16))) char sm_lds[];
   u32x4* gt = reinterpret_cast<u32x4*>(sm_lds);
   auto xs = [&](int buf) { return reinterpret_cast<u32x4*>(sm_lds + Lds::kXs + buf * Lds::kXbuf); };
@@ -154,7 +171,8 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
   uint32_t* vt = reinterpret_cast<uint32_t*>(sm_lds + Lds::kVt) + (threadIdx.x >> 6) * NV * 64;  // this wave's tail words
   const int T = L.T, r = L.r, d_in = L.d_in, mt = L.mt;
   const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int grp4 = wv / kWaves, wave = wv % kWaves;  // group of 4 waves; the wave's role in it
   const int n16 = lane & 15, gq = lane >> 4;
   const rsrc_t vr = make_rsrc_uniform(p ? L.V[1] : L.V[0], L.v_bytes);
   const rsrc_t gr = make_rsrc_uniform(p ? L.g[1] : L.g[0], L.g_bytes);
@@ -188,11 +206,12 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
     if constexpr (TT == 1) {
 #pragma unroll
       for (int f = 0; f < CB * XC; ++f)
-        load_x4(reinterpret_cast<char*>(xs(buf) + f * 64), 0, 32 * (bb + f / XC) + 4 * (f % XC), wave, true);
+        if (f / XC % G == grp4)
+          load_x4(reinterpret_cast<char*>(xs(buf) + f * 64), 0, 32 * (bb + f / XC) + 4 * (f % XC), wave, true);
     } else {
 #pragma unroll
       for (int i = 0; i < XI; ++i) {
-        const int f = wave + kWaves * i;  // (block, token tile, piece), piece fastest
+        const int f = wv + NWV * i;  // (block, token tile, piece), piece fastest
         const int pc = f % XC, tt = (f / XC) % TT, bl = f / (XC * TT);
         char* dst = reinterpret_cast<char*>(xs(buf) + f * 64);
         const int j = 32 * (bb + bl) + 4 * pc;  // piece pc of lane group gq: inputs j + 8 gq ..
@@ -207,15 +226,17 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
       }
     }
 #pragma unroll
-    for (int bl = 0; bl < CB; ++bl)
+    for (int b = 0; b < CB / G; ++b)
 #pragma unroll
-      for (int d = 0; d < NV; ++d)
+      for (int d = 0; d < NV; ++d) {
+        const int bl = G * b + grp4;
         // (32-bit tail entries sit where a full word would)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_ptr)(vs(buf, bl, wave) + 64 * d), 4,
                                                  (static_cast<uint32_t>(bb + bl) * r + vlane + 64 * d) * 4u, 0, 0, 0);
+      }
   };
 #pragma unroll
-  for (int ch = 0; ch < kBuf1 - 1; ++ch) load(ch, ch);
+  for (int ch = 0; ch < kBuf - 1; ++ch) load(ch, ch);
 
   if (tail16)
 #pragma unroll
@@ -225,7 +246,7 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
           __builtin_amdgcn_raw_buffer_load_b16(vr, k < r ? 4u * nbv * r + 2u * k : kOob, 0, 0));
     }
   // the run's g terms (zero past d_in): [block][lane group][term]
-  for (int it = tid; it < (b1 - b0) * 4; it += kThreads) {
+  for (int it = tid; it < (b1 - b0) * 4; it += NWV * 64) {
     const uint32_t j0 = 32 * (b0 + (it >> 2)) + 4 * (it & 3);
     uint32_t raw[2][4];
     bload4<SC, true>(gr, j0, true, raw[0]);
@@ -307,30 +328,47 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
       }
     }
   };
-  constexpr int kAhead = kBuf1 - 2;  // chunks still in flight when one is used
+  constexpr int kAhead = kBuf - 2;  // chunks still in flight when one is used
   int buf = 0;
   for (int ch = 0; ch < nch; ++ch) {
     // chunk ch has landed (each wave waits for its own loads, the barrier for
     // everyone's) and every wave is done with the buffer of chunk ch - 1
     if (TT == 1)
-      wait_barrier<kAhead * CB * (XC + NV)>();
+      wait_barrier<kAhead * Lds::kOps>();
     else if (xv)
-      wait_barrier<kAhead * (XI + CB * NV)>();
+      wait_barrier<kAhead * (XI + Lds::kVops)>();
     else
-      wait_barrier<kAhead * (4 * XI + CB * NV)>();
-    load(ch + kBuf1 - 1, buf == 0 ? kBuf1 - 1 : buf - 1);
+      wait_barrier<kAhead * Lds::kOps>();
+    load(ch + kBuf - 1, buf == 0 ? kBuf - 1 : buf - 1);
     if (mts > 0) {
 #pragma unroll
-      for (int bl = 0; bl < CB; ++bl) {
-        const int b = b0 + ch * CB + bl;
+      for (int i = 0; i < CB / G; ++i) {
+        const int bl = G * i + grp4, b = b0 + ch * CB + bl;
         if (b < b1) block(b, buf, bl);
       }
     }
-    buf = buf == kBuf1 - 1 ? 0 : buf + 1;
+    buf = buf == kBuf - 1 ? 0 : buf + 1;
   }
   // global-to-LDS loads past the run are still in flight: none may land after
   // the workgroup's LDS is given away
   __builtin_amdgcn_s_waitcnt(0);
+  if constexpr (ONE) {
+    // the groups' sums, (0 + 2) + (1 + 3), through LDS
+    static_assert(kGroups == 4, "two steps");
+    floatx4* red = reinterpret_cast<floatx4*>(sm_lds) + wave * MT * TT * 64 + lane;
+#pragma unroll
+    for (int n = 2; n >= 1; n >>= 1) {
+      __syncthreads();
+      if (grp4 >= n && grp4 < 2 * n)
+#pragma unroll
+        for (int m = 0; m < MT * TT; ++m) red[((grp4 - n) * kWaves * MT * TT + m) * 64] = acc[m / TT][m % TT];
+      __syncthreads();
+      if (grp4 < n)
+#pragma unroll
+        for (int m = 0; m < MT * TT; ++m) acc[m / TT][m % TT] += red[(grp4 * kWaves * MT * TT + m) * 64];
+    }
+    if (grp4 > 0) return;
+  }
   if (mts <= 0) return;
   float* out = L.part + (static_cast<int64_t>(p * L.s1d + c) * nmf + t0) * TT * 256 + lane * 4;
 #pragma unroll
@@ -346,7 +384,7 @@ __global__ void __launch_bounds__(kThreads) sm_s1_kernel(const uint32_t* __restr
                                                          const uint32_t* __restrict__ map, uint64_t fp) {
   if (!plan_ok(hdr, fp)) return;
   const uint32_t code = map[blockIdx.x];
-  sm_s1_body<TT, MT, ACT, SC>(descs[code >> 16], (code >> 15) & 1, (code >> 9) & 63, code & 511);
+  sm_s1_body<TT, MT, ACT, SC, false>(descs[code >> 16], (code >> 15) & 1, (code >> 9) & 63, code & 511);
 }
 
 // ---------------------------------------------------------------------------
@@ -367,7 +405,10 @@ __host__ __device__ inline size_t frag_bytes(int T, int r, int nw) {
 // threads of R for one linear
 __host__ __device__ inline int r_items(int T, int r) { return 2 * ((T + 15) / 16) * nblocks32(r) * 64; }
 
-template <int NW, int SC>
+// ONE (one linear, few threads): a workgroup's 4 waves share the fragment,
+// each adding a quarter of the runs, and the quarters are added in order: the
+// sum is one round of loads instead of four (6.5 us at 16 runs).
+template <int NW, int SC, bool ONE>
 __device__ __forceinline__ void sm_r_body(const StreamLinear& L, int e) {
   const int T = L.T, r = L.r, s1d = L.s1d;
   if (e >= r_items(T, r)) return;
@@ -380,19 +421,43 @@ __device__ __forceinline__ void sm_r_body(const StreamLinear& L, int e) {
   const float* src = L.part + ((static_cast<int64_t>(p) * s1d * nmf + 2 * kb) * tt_n + tt) * 256 + lane * 4;
   const int64_t cs = static_cast<int64_t>(nmf) * tt_n * 256;
   const int64_t hs = two ? tt_n * 256 : 0;
+  const rsrc_t lr = make_rsrc(p ? L.l[1] : L.l[0], L.l_bytes);
+  floatx4 l0, l1;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int k = 32 * kb + 4 * gq + v;
+    l0[v] = bits_to_f32<SC>(bload<SC>(lr, k, k < r));
+    l1[v] = bits_to_f32<SC>(bload<SC>(lr, k + 16, k + 16 < r));
+  }
   floatx4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
-#pragma unroll 4
-  for (int c = 0; c < s1d; ++c) {
+  const int wave = threadIdx.x >> 6;
+  const int per = (s1d + kWaves - 1) / kWaves;
+  const int c0 = ONE ? min(s1d, wave * per) : 0, c1 = ONE ? min(s1d, c0 + per) : s1d;
+#pragma unroll 8
+  for (int c = c0; c < c1; ++c) {
     z0 += *reinterpret_cast<const floatx4*>(src + c * cs);
     z1 += *reinterpret_cast<const floatx4*>(src + c * cs + hs);
   }
-  const rsrc_t lr = make_rsrc(p ? L.l[1] : L.l[0], L.l_bytes);
+  if constexpr (ONE) {
+    __shared__ floatx4 part[kWaves - 1][2][64];
+    if (wave > 0) {
+      part[wave - 1][0][lane] = z0;
+      part[wave - 1][1][lane] = z1;
+    }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 0; w < kWaves - 1; ++w) {
+      z0 += part[w][0][lane];
+      z1 += part[w][1][lane];
+    }
+  }
   uint32_t lo[4][NW], hi[4][NW];
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int k = 32 * kb + 4 * gq + v;
-    split_round<NW>(k < r ? z0[v] * bits_to_f32<SC>(bload<SC>(lr, k, k < r)) : 0.0f, lo[v]);
-    split_round<NW>(k + 16 < r ? z1[v] * bits_to_f32<SC>(bload<SC>(lr, k + 16, k + 16 < r)) : 0.0f, hi[v]);
+    split_round<NW>(k < r ? z0[v] * l0[v] : 0.0f, lo[v]);
+    split_round<NW>(k + 16 < r ? z1[v] * l1[v] : 0.0f, hi[v]);
   }
   u32x4* frag = reinterpret_cast<u32x4*>(L.wlat) + static_cast<int64_t>(f) * NW * 64 + lane;
 #pragma unroll
@@ -407,15 +472,15 @@ __global__ void __launch_bounds__(kThreads) sm_r_kernel(const uint32_t* __restri
                                                         const uint32_t* __restrict__ map, uint64_t fp) {
   if (!plan_ok(hdr, fp)) return;
   const uint32_t code = map[blockIdx.x];
-  sm_r_body<NW, SC>(descs[code >> 16], static_cast<int>(code & 0xffffu) * kThreads + threadIdx.x);
+  sm_r_body<NW, SC, false>(descs[code >> 16], static_cast<int>(code & 0xffffu) * kThreads + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
 // S2: 64 RB output rows of one linear, every token, both paths.  Wave w holds
 // row tiles RB w .. RB w + RB - 1 of 16 rows for every token tile.  The B
 // fragments (shared by the waves) and each wave's U words stream through
-// kBuf2 LDS buffers in chunks of kCk 32-latent blocks (path 0, then path 1),
-// filled by global-to-LDS loads kBuf2 - 1 chunks ahead, one barrier a chunk.
+// a ring of LDS buffers in chunks of kCk 32-latent blocks (path 0, then path 1),
+// filled by global-to-LDS loads kBuf - 1 chunks ahead, one barrier a chunk.
 // Up to 16 tokens the A operands bound it (9 VALU instructions for 2 matrix
 // instructions), from 32 on the matrix cores.
 // ---------------------------------------------------------------------------
@@ -427,23 +492,29 @@ __host__ __device__ constexpr int rb_of(int tt) { return tt == 1 ? 8 : 4; }
 
 // LDS of S2 (one array, as in S1): the fragment and U-word buffers, the 16-bit
 // tail words
-template <int TT, int RB, int ACT>
+template <int TT, int RB, int ACT, bool ONE = false>
 struct S2Lds {
-  static constexpr int FI = (kCk * TT * nw_of(ACT) + kWaves - 1) / kWaves;
+  static constexpr int G = ONE ? kGroups : 1, NWV = G * kWaves, CK = ONE ? G : kCk;
+  static constexpr int FI = (CK * TT * nw_of(ACT) + NWV - 1) / NWV;
   static constexpr int NV = (RB + 3) / 4;
-  static constexpr int kBbuf = FI * kWaves * 1024;
-  static constexpr int kUs = kBuf2 * kBbuf;
-  static constexpr int kUt = kUs + kBuf2 * kCk * kWaves * NV * 256;
-  static constexpr int kBytes = kUt + 2 * kWaves * NV * 256;
+  static constexpr int kBbuf = FI * NWV * 1024;
+  static constexpr int kUbuf = CK * kWaves * NV * 256;
+  static constexpr int kDeep = static_cast<int>(kOneLds / (kBbuf + kUbuf));
+  static constexpr int kBuf = !ONE ? kBuf2 : (kDeep < kOneBuf ? kDeep : kOneBuf);
+  static constexpr int kUs = kBuf * kBbuf;
+  static constexpr int kUt = kUs + kBuf * kUbuf;
+  static constexpr int kRed = 2 * kWaves * RB * TT * 1024;
+  static constexpr int kRing = kUt + 2 * kWaves * NV * 256;
+  static constexpr int kBytes = ONE && kRed > kRing ? kRed : kRing;
 };
 
-template <int TT, int RB, int ACT, int SC>
+template <int TT, int RB, int ACT, int SC, bool ONE>
 __device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
-  constexpr int NW = nw_of(ACT), CK = kCk;
-  constexpr int kFr = CK * TT * NW;                // fragments (1 KB) of a chunk
-  constexpr int FI = (kFr + kWaves - 1) / kWaves;  // of them per wave
+  constexpr int NW = nw_of(ACT);
   constexpr int NV = (RB + 3) / 4;                 // word loads (64 rows) per wave and block
-  using Lds = S2Lds<TT, RB, ACT>;
+  using Lds = S2Lds<TT, RB, ACT, ONE>;
+  constexpr int kBuf = Lds::kBuf, G = Lds::G, NWV = Lds::NWV, CK = Lds::CK;
+  constexpr int FI = Lds::FI;                      // fragments (1 KB) of a chunk per wave
   extern __shared__ __attribute__((aligned(16))) char sm_lds[];
   auto bs = [&](int buf) { return reinterpret_cast<u32x4*>(sm_lds + buf * Lds::kBbuf); };
   auto us = [&](int buf, int u, int w) {
@@ -454,7 +525,8 @@ __device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
   };
   const int T = L.T, r = L.r, d_out = L.d_out;
   const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int grp4 = wv / kWaves, wave = wv % kWaves;  // group of 4 waves; the wave's role in it
   const int n16 = lane & 15, gq = lane >> 4;
   const int nkb = nblocks32(r), nbu = r >> 5, tailu = r & 31;
   const int nch = (nkb + CK - 1) / CK;  // chunks per path
@@ -466,27 +538,29 @@ __device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
   // chunk ci (path ci / nch): FI fragment and NV CK word loads per wave.
   // Fragments past a path's blocks and words past a block's rows are whatever
   // is there (zero past the buffers): no product of theirs is kept.
-  const uint32_t flane = wave * 1024u + lane * 16u, ulane = row0 + lane;
+  const uint32_t flane = wv * 1024u + lane * 16u, ulane = row0 + lane;
   auto load = [&](int ci, int buf) {
     const int p = ci >= nch ? 1 : 0, kb0 = (ci - p * nch) * CK;
     const uint32_t f0 = static_cast<uint32_t>((p * nkb + kb0) * TT * NW) * 1024u + flane;
 #pragma unroll
     for (int i = 0; i < FI; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(fr, (lds_ptr)(bs(buf) + (wave + kWaves * i) * 64), 16,
-                                               f0 + kWaves * i * 1024u, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(fr, (lds_ptr)(bs(buf) + (wv + NWV * i) * 64), 16,
+                                               f0 + NWV * i * 1024u, 0, 0, 0);
     const rsrc_t ur = p ? ur1 : ur0;
 #pragma unroll
-    for (int u = 0; u < CK; ++u)
+    for (int i = 0; i < CK / G; ++i)
 #pragma unroll
-      for (int d = 0; d < NV; ++d)
+      for (int d = 0; d < NV; ++d) {
+        const int u = G * i + grp4;
         // (32-bit tail entries sit where a full word would)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ur, (lds_ptr)(us(buf, u, wave) + 64 * d), 4,
                                                  (static_cast<uint32_t>(kb0 + u) * d_out + ulane + 64 * d) * 4u, 0, 0,
                                                  0);
+      }
   };
 #pragma unroll
-  for (int ci = 0; ci < kBuf2 - 1; ++ci) load(ci, ci);
-  if (tail16)
+  for (int ci = 0; ci < kBuf - 1; ++ci) load(ci, ci);
+  if (tail16 && grp4 == 0)
 #pragma unroll
     for (int pp = 0; pp < 2; ++pp)
 #pragma unroll
@@ -519,17 +593,17 @@ __device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
   };
   int buf = 0;
 #pragma unroll 1
-  for (int ci = 0; ci < 2 * nch; ++ci, buf = buf == kBuf2 - 1 ? 0 : buf + 1) {
+  for (int ci = 0; ci < 2 * nch; ++ci, buf = buf == kBuf - 1 ? 0 : buf + 1) {
     // chunk ci has landed (each wave waits for its own loads, the barrier for
     // everyone's) and every wave is done with the buffer of chunk ci - 1
-    wait_barrier<(kBuf2 - 2) * (FI + NV * CK)>();
-    load(ci + kBuf2 - 1, buf == 0 ? kBuf2 - 1 : buf - 1);
+    wait_barrier<(kBuf - 2) * (FI + NV * CK / G)>();
+    load(ci + kBuf - 1, buf == 0 ? kBuf - 1 : buf - 1);
     if (!active) continue;
     const int p = ci >= nch ? 1 : 0, kb0 = (ci - p * nch) * CK;
     if (ci == nch) fold(0);
 #pragma unroll
-    for (int u = 0; u < CK; ++u) {
-      const int kb = kb0 + u;
+    for (int i = 0; i < CK / G; ++i) {
+      const int u = G * i + grp4, kb = kb0 + u;
       if (kb >= nkb) break;
       const uint32_t* wp = tail16 && kb == nbu ? ut(p, wave) : us(buf, u, wave);
       uint32_t words[RB];
@@ -555,8 +629,24 @@ __device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
   // global-to-LDS loads past the end are still in flight: none may land after
   // the workgroup's LDS is given away
   __builtin_amdgcn_s_waitcnt(0);
+  if (active) fold(1);
+  if constexpr (ONE) {
+    // the groups' shares of y, (0 + 2) + (1 + 3), through LDS
+    floatx4* red = reinterpret_cast<floatx4*>(sm_lds) + wave * RB * TT * 64 + lane;
+#pragma unroll
+    for (int n = 2; n >= 1; n >>= 1) {
+      __syncthreads();
+      if (grp4 >= n && grp4 < 2 * n)
+#pragma unroll
+        for (int m = 0; m < RB * TT; ++m) red[((grp4 - n) * kWaves * RB * TT + m) * 64] = yv[m / TT][m % TT];
+      __syncthreads();
+      if (grp4 < n)
+#pragma unroll
+        for (int m = 0; m < RB * TT; ++m) yv[m / TT][m % TT] += red[(grp4 * kWaves * RB * TT + m) * 64];
+    }
+    if (grp4 > 0) return;
+  }
   if (!active) return;
-  fold(1);
   // 4 consecutive outputs per lane and token
   const bool vec = d_out % 4 == 0 && reinterpret_cast<uintptr_t>(L.y) % (ACT == kDtF32 ? 16 : 8) == 0;
 #pragma unroll
@@ -593,12 +683,38 @@ __global__ void __launch_bounds__(kThreads) sm_s2_kernel(const uint32_t* __restr
                                                          const uint32_t* __restrict__ map, uint64_t fp) {
   if (!plan_ok(hdr, fp)) return;
   const uint32_t code = map[blockIdx.x];
-  sm_s2_body<TT, rb_of(TT), ACT, SC>(descs[code >> 16], static_cast<int>(code & 0xffffu));
+  sm_s2_body<TT, rb_of(TT), ACT, SC, false>(descs[code >> 16], static_cast<int>(code & 0xffffu));
 }
 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+void fill_desc(StreamLinear& L, const ForwardArgs& f, const SmGeom& g) {
+  L.x = f.x;
+  L.y = f.y;
+  for (int p = 0; p < 2; ++p) {
+    L.U[p] = f.U[p];
+    L.V[p] = f.V[p];
+    L.h[p] = f.h[p];
+    L.g[p] = f.g[p];
+    L.l[p] = f.l[p];
+  }
+  L.T = f.T;
+  L.d_in = f.d_in;
+  L.d_out = f.d_out;
+  L.r = f.r;
+  L.s1d = g.s1d;
+  L.bpr = g.bpr;
+  L.mt = g.mt;
+  const int64_t ex = f.act_dt == kDtF32 ? 4 : 2, es = f.sc_dt == kDtF32 ? 4 : 2;
+  L.x_bytes = static_cast<uint32_t>(static_cast<int64_t>(f.T) * f.d_in * ex);
+  L.g_bytes = static_cast<uint32_t>(f.d_in * es);
+  L.h_bytes = static_cast<uint32_t>(f.d_out * es);
+  L.l_bytes = static_cast<uint32_t>(f.r * es);
+  L.v_bytes = static_cast<uint32_t>(packed_bytes64(f.r, f.d_in));
+  L.u_bytes = static_cast<uint32_t>(packed_bytes64(f.d_out, f.r));
+}
+
 struct PlanLayout {
   int bpr = kMaxBpr;
   int n1 = 0, nr = 0, n2 = 0;
@@ -745,31 +861,9 @@ hipError_t stream_mma_init(const ForwardArgs* a, int n, uint64_t fp, void* ws, h
   for (int i = 0; i < n; ++i) {
     StreamLinear& L = D[i];
     const ForwardArgs& f = a[i];
-    L.x = f.x;
-    L.y = f.y;
-    for (int p = 0; p < 2; ++p) {
-      L.U[p] = f.U[p];
-      L.V[p] = f.V[p];
-      L.h[p] = f.h[p];
-      L.g[p] = f.g[p];
-      L.l[p] = f.l[p];
-    }
-    L.T = f.T;
-    L.d_in = f.d_in;
-    L.d_out = f.d_out;
-    L.r = f.r;
     if (!has_work(f)) continue;
     const SmGeom g = sm_geometry(f, P.bpr);
-    L.s1d = g.s1d;
-    L.bpr = g.bpr;
-    L.mt = g.mt;
-    const int64_t ex = f.act_dt == kDtF32 ? 4 : 2, es = f.sc_dt == kDtF32 ? 4 : 2;
-    L.x_bytes = static_cast<uint32_t>(static_cast<int64_t>(f.T) * f.d_in * ex);
-    L.g_bytes = static_cast<uint32_t>(f.d_in * es);
-    L.h_bytes = static_cast<uint32_t>(f.d_out * es);
-    L.l_bytes = static_cast<uint32_t>(f.r * es);
-    L.v_bytes = static_cast<uint32_t>(packed_bytes64(f.r, f.d_in));
-    L.u_bytes = static_cast<uint32_t>(packed_bytes64(f.d_out, f.r));
+    fill_desc(L, f, g);
     L.part = reinterpret_cast<float*>(data);
     data += align256(part_bytes(g));
     L.wlat = reinterpret_cast<float*>(data);  // the B fragments of stage 2
@@ -805,6 +899,164 @@ hipError_t stream_mma_forward(const ForwardArgs* a, int n, uint64_t fp, void* ws
     default: launch_act<kDtBF16>(ws, P, sc, fp, stream); break;
   }
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// One linear of up to 64 tokens, or a few of one token tile count: the same
+// three stages, the descriptors as a kernel argument (grid y: the linear).  A
+// linear's runs and wave groups do not depend on the others, so its result has
+// the same bits alone and among others.
+// ---------------------------------------------------------------------------
+namespace {
+
+constexpr int kOneThreads = kGroups * kThreads;
+
+struct FewArgs {
+  StreamLinear l[kFewMaxBatch];
+};
+
+template <int TT, int MT, int ACT, int SC>
+__global__ void __launch_bounds__(kOneThreads) sm_one_s1_kernel(FewArgs A) {
+  const StreamLinear& L = A.l[blockIdx.y];
+  const int rest = blockIdx.x / L.s1d;
+  if ((rest >> 1) * kWaves * L.mt >= (L.r + 15) >> 4) return;  // past this linear's groups
+  sm_s1_body<TT, MT, ACT, SC, true>(L, rest & 1, rest >> 1, blockIdx.x - rest * L.s1d);
+}
+template <int NW, int SC>
+__global__ void __launch_bounds__(kThreads) sm_one_r_kernel(FewArgs A) {
+  const StreamLinear& L = A.l[blockIdx.y];
+  sm_r_body<NW, SC, true>(L, blockIdx.x * 64 + (threadIdx.x & 63));
+}
+template <int TT, int ACT, int SC>
+__global__ void __launch_bounds__(kOneThreads) sm_one_s2_kernel(FewArgs A) {
+  const StreamLinear& L = A.l[blockIdx.y];
+  if (static_cast<int>(blockIdx.x) * 16 * kWaves >= L.d_out) return;
+  sm_s2_body<TT, 1, ACT, SC, true>(L, blockIdx.x);
+}
+
+constexpr int kOneWantWg = 192;  // S1 workgroups wanted
+constexpr int kOneMaxRuns = 16;  // runs at most: R adds them
+constexpr int kOneMinBpr = 8;    // 32-input blocks of a run at least: two per wave group
+// largest tile class of a 16-wave workgroup (128 registers a lane)
+constexpr int one_max_cls(int tt) { return tt == 1 ? 3 : (tt == 2 ? 2 : 1); }
+
+// the plan of one linear in ws_bytes of workspace (bpr 0: none fits): as many
+// runs as give kOneWantWg workgroups, fewer tiles a wave when they do not
+SmGeom one_geometry(const ForwardArgs& a, size_t ws_bytes) {
+  SmGeom g = sm_geometry(a, kMaxBpr);
+  const int nbt = nblocks32(a.d_in);
+  const size_t room = ws_bytes - kCtrlBytes;
+  const size_t frag = align256(frag_bytes(a.T, a.r, nw_of(a.act_dt)));
+  const int max_runs = std::max(1, std::min(kOneMaxRuns, nbt / kOneMinBpr));
+  int c = one_max_cls(g.tt);
+  for (;; --c) {
+    g.ng = (g.nmf + kWaves * mt_cls(g.tt, c) - 1) / (kWaves * mt_cls(g.tt, c));
+    if (c == 0 || 2 * g.ng * max_runs >= kOneWantWg) break;
+  }
+  g.mt = (g.nmf + kWaves * g.ng - 1) / (kWaves * g.ng);
+  g.cls = (g.tt - 1) * kMtClasses + c;
+  int runs = std::max(1, std::min(max_runs, (kOneWantWg + 2 * g.ng - 1) / (2 * g.ng)));
+  runs = std::max(runs, (nbt + kMaxBpr - 1) / kMaxBpr);
+  for (;; --runs) {
+    g.bpr = (nbt + runs - 1) / runs;
+    g.s1d = (nbt + g.bpr - 1) / g.bpr;
+    if (g.bpr > kMaxBpr) {
+      g.bpr = 0;  // no room
+      return g;
+    }
+    if (align256(part_bytes(g)) + frag <= room) return g;
+    if (runs == 1) {
+      g.bpr = 0;
+      return g;
+    }
+  }
+}
+
+// a kernel with more than 64 KB of dynamic LDS: its limit is raised once
+template <typename K>
+hipError_t allow_lds(K* fn, int bytes, std::atomic<bool>& done) {
+  if (bytes <= 65536 || done.load()) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.store(true);
+  return e;
+}
+template <int TT, int C, int ACT, int SC>
+hipError_t one_s1(const FewArgs& A, int n, int n1, hipStream_t stream) {
+  constexpr int MT = mt_cls(TT, C), bytes = S1Lds<TT, MT, ACT, SC, true>::kBytes;
+  static std::atomic<bool> done{false};
+  const hipError_t e = allow_lds(&sm_one_s1_kernel<TT, MT, ACT, SC>, bytes, done);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((sm_one_s1_kernel<TT, MT, ACT, SC>), dim3(n1, n), dim3(kOneThreads), bytes, stream, A);
+  return hipGetLastError();
+}
+template <int TT, int ACT, int SC>
+hipError_t one_launch(const FewArgs& A, int n, int c, int n1, int nr, int n2, hipStream_t stream) {
+  constexpr int bytes = S2Lds<TT, 1, ACT, true>::kBytes;
+  static std::atomic<bool> done{false};
+  hipError_t e = allow_lds(&sm_one_s2_kernel<TT, ACT, SC>, bytes, done);
+  if (e != hipSuccess) return e;
+  constexpr int most = one_max_cls(TT);
+  if (c == 0)
+    e = one_s1<TT, 0, ACT, SC>(A, n, n1, stream);
+  else if (c == 1)
+    e = one_s1<TT, 1, ACT, SC>(A, n, n1, stream);
+  else if (c == 2)
+    e = one_s1<TT, (most < 2 ? most : 2), ACT, SC>(A, n, n1, stream);
+  else
+    e = one_s1<TT, most, ACT, SC>(A, n, n1, stream);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((sm_one_r_kernel<nw_of(ACT), SC>), dim3(nr, n), dim3(kThreads), 0, stream, A);
+  hipLaunchKernelGGL((sm_one_s2_kernel<TT, ACT, SC>), dim3(n2, n), dim3(kOneThreads), bytes, stream, A);
+  return hipGetLastError();
+}
+template <int ACT, int SC>
+hipError_t one_tt(const FewArgs& A, int n, int tt, int c, int n1, int nr, int n2, hipStream_t stream) {
+  switch (tt) {
+    case 1: return one_launch<1, ACT, SC>(A, n, c, n1, nr, n2, stream);
+    case 2: return one_launch<2, ACT, SC>(A, n, c, n1, nr, n2, stream);
+    case 3: return one_launch<3, ACT, SC>(A, n, c, n1, nr, n2, stream);
+    default: return one_launch<4, ACT, SC>(A, n, c, n1, nr, n2, stream);
+  }
+}
+template <int ACT>
+hipError_t one_sc(int sc_dt, const FewArgs& A, int n, int tt, int c, int n1, int nr, int n2, hipStream_t stream) {
+  switch (sc_dt) {
+    case kDtF32: return one_tt<ACT, kDtF32>(A, n, tt, c, n1, nr, n2, stream);
+    case kDtF16: return one_tt<ACT, kDtF16>(A, n, tt, c, n1, nr, n2, stream);
+    default: return one_tt<ACT, kDtBF16>(A, n, tt, c, n1, nr, n2, stream);
+  }
+}
+
+}  // namespace
+
+bool few_tokens_supports(const ForwardArgs& a, size_t ws_bytes) {
+  return stream_mma_supports(a) && has_work(a) && ws_bytes > kCtrlBytes && one_geometry(a, ws_bytes).bpr > 0;
+}
+
+hipError_t launch_few_tokens(const ForwardArgs* a, const size_t* ws_bytes, int n, hipStream_t stream) {
+  if (n < 1 || n > kFewMaxBatch) return hipErrorInvalidValue;
+  FewArgs A{};
+  const int tt = (a[0].T + 15) / 16;
+  int c = 0, n1 = 0, nr = 0, n2 = 0;  // the largest tile class and grids
+  for (int i = 0; i < n; ++i) {
+    if ((a[i].T + 15) / 16 != tt || a[i].act_dt != a[0].act_dt || a[i].sc_dt != a[0].sc_dt) return hipErrorInvalidValue;
+    const SmGeom g = one_geometry(a[i], ws_bytes[i]);
+    StreamLinear& L = A.l[i];
+    fill_desc(L, a[i], g);
+    char* data = static_cast<char*>(a[i].ws) + kCtrlBytes;
+    L.part = reinterpret_cast<float*>(data);
+    L.wlat = reinterpret_cast<float*>(data + align256(part_bytes(g)));
+    c = std::max(c, g.cls % kMtClasses);
+    n1 = std::max(n1, 2 * g.ng * g.s1d);
+    nr = std::max(nr, r_items(L.T, L.r) / 64);
+    n2 = std::max(n2, (L.d_out + 16 * kWaves - 1) / (16 * kWaves));
+  }
+  switch (a[0].act_dt) {
+    case kDtF32: return one_sc<kDtF32>(a[0].sc_dt, A, n, tt, c, n1, nr, n2, stream);
+    case kDtF16: return one_sc<kDtF16>(a[0].sc_dt, A, n, tt, c, n1, nr, n2, stream);
+    default: return one_sc<kDtBF16>(a[0].sc_dt, A, n, tt, c, n1, nr, n2, stream);
+  }
 }
 
 }  // namespace lb

@@ -374,3 +374,46 @@ def test_graph_replays_match_eager(T, kernel):
         else:
             _check(li, U.torch_to_raw(y_graph, "bf16"), label=f"graph replay {rep}")
             _check(li, U.torch_to_raw(y_mid, "bf16"), label=f"eager between replays {rep}")
+
+
+# ---------------------------------------------------------------------------
+# the few-token stages (AUTO, 16 to 64 tokens; fewer where r d_out >= 8e6)
+# ---------------------------------------------------------------------------
+# tile classes and groups of latents at their edges, one run and several, runs whose wave groups get unequal shares of
+# blocks, tails of d_in and r, rows that are not whole 16-byte pieces, outputs around the 64-row workgroups
+FEW = [(16, 128, 64, 16), (16, 36, 65, 129), (17, 2092, 63, 33), (31, 4096, 200, 320), (32, 1000, 127, 50),
+       (33, 288, 1, 193), (48, 3000, 257, 288), (49, 64, 500, 385), (64, 11008, 96, 800), (64, 260, 1000, 577),
+       (20, 4100, 129, 641), (3, 520, 10000, 816)]
+
+
+@pytest.mark.parametrize("case", FEW, ids=[f"T{c[0]}_{c[1]}x{c[2]}r{c[3]}" for c in FEW])
+@pytest.mark.parametrize("act,sc", [("bf16", "f16"), ("f32", "f32"), ("f16", "bf16")])
+def test_few_tokens_edges(case, act, sc):
+    T, d_in, d_out, r = case
+    li = synth.make_linear(d_in, d_out, r, T, act_dtype=act, scale_dtype=sc, cfg=91, linear=T + d_in, l_over_sqrt_r=True)
+    y_raw = _run(li)
+    _check(li, y_raw, label=f"{case} {act}/{sc}")
+
+
+def test_few_tokens_many_and_shared_workspace():
+    # alone, among others of one launch, and between calls of other kernels on one workspace: the same bits
+    specs = [(16, 1024, 700, 80), (24, 512, 900, 300), (16, 96, 64, 16), (16, 2048, 130, 530), (31, 640, 640, 64),
+             (40, 512, 256, 48), (16, 160, 33, 200), (16, 320, 1025, 20), (16, 224, 96, 96), (16, 4096, 64, 128),
+             (16, 64, 64, 64)]
+    lins = [synth.make_linear(d_in, d_out, r, T, act_dtype="bf16", scale_dtype="f16", cfg=92, linear=i,
+                              l_over_sqrt_r=True) for i, (T, d_in, d_out, r) in enumerate(specs)]
+    items = []
+    for li in lins:
+        x, paths, _ = U.to_device(li, True)
+        items.append((x, paths, li.r, None))
+    alone = [lb.lb_linear_forward(x, paths, r) for x, paths, r, _ in items]
+    many = lb.lb_linear_forward_many(items)
+    ws = max((lb.alloc_workspace(li.T, li.d_in, li.d_out, li.r) for li in lins), key=lambda t: t.numel())
+    for rep in range(2):
+        for (x, paths, r, _), y in zip(items, alone):
+            assert torch.equal(lb.lb_linear_forward(x, paths, r, workspace=ws), y)
+            one = lb.lb_linear_forward(x[:1].contiguous(), paths, r, workspace=ws)  # look-up-table kernel
+            assert torch.equal(one, lb.lb_linear_forward(x[:1].contiguous(), paths, r))
+    torch.cuda.synchronize()
+    for y, z in zip(alone, many):
+        assert torch.equal(y, z)
