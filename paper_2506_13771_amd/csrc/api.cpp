@@ -124,11 +124,13 @@ lb_kernel auto_kernel(int64_t T, int64_t d_in, int64_t d_out, int64_t r) {
 // 7B, 13B and 70B shapes: 16 tokens 12-21 (17-42 matrix-core decode), 32 tokens
 // 12-24 (15-45 prefill), 64 tokens 14-32 (15-50), except past 48 tokens with
 // very many outputs, where prefill's larger output units win (8192 -> 28672, r =
-// 304: 28.4 against 27.5).  Below 16 tokens the single-launch kernels stay,
-// which a list of calls batches, unless prefill would run (r d_out >= 8e6).
+// 304: 28.4 against 27.5).  Below 16 tokens one launch beats three while r d_out
+// is small (8 tokens, 4096 -> 4096: r = 80 13.4 decode; 4096 -> 11008, r = 128
+// 15.0 against 16.8; 3 tokens, r = 544 18.0 against 23.0).
 bool prefer_few(const lb::ForwardArgs& a) {
   if (a.T <= kAutoLutTokens || a.T > 64 || (a.T > 48 && a.d_out > 16384)) return false;
-  if (a.T < 16 && !prefer_prefill(a.T, a.d_out, a.r)) return false;
+  const int64_t rd = static_cast<int64_t>(a.r) * a.d_out;
+  if (a.T < 16 && !(a.T >= 8 && rd >= 1000000) && rd < 2000000) return false;
   return lb::few_tokens_supports(a, lb_forward_workspace_bytes(a.T, a.d_in, a.d_out, a.r));
 }
 
