@@ -95,7 +95,7 @@ struct PrefillParams {
   int ns16p;        // P1 partial subtile slots per path
   int n_un, n_og, n_tt2;  // P2 units, unit groups, token tiles
   int res, kbc;     // P2: w resident / blocks per chunk
-  int xdma;         // x rows are whole 16-byte chunks: global-to-LDS loads
+  int xdma;         // x by global-to-LDS loads: 1 rows are whole 16-byte chunks, 2 whole dwords; 0 element loads
   int vw;           // P1 V words in 16-byte loads (r % 4 == 0, V 16-byte aligned)
   int fast;         // P2 fast path (see prefill_p2)
   uint32_t v_bytes, u_bytes, g_bytes, h_bytes, l_bytes, wt_bytes;
@@ -133,7 +133,9 @@ __host__ __device__ constexpr size_t p1_lds(int kb_per, int G, int act, int ms, 
   return ring > red ? ring : red;
 }
 
-template <int MS, int ACT, int SC, bool VW>
+// XV: x rows are whole 16-byte chunks (xdma 1); else dword or element loads (a
+// choice per call, kept out of the other form's loop, where it cost 1-2%)
+template <int MS, int ACT, int SC, bool VW, bool XV>
 __global__ void __launch_bounds__(kThreads1, 1) prefill_p1(PrefillParams P) {
   constexpr int G = nterms<SC>(), E = nterms<ACT>();
   constexpr int NX = p1_nx(ACT), NV = p1_nv(MS, VW), RING = p1_ring(ACT), RR = RING / kSplit1;
@@ -194,7 +196,7 @@ __global__ void __launch_bounds__(kThreads1, 1) prefill_p1(PrefillParams P) {
     }
     const int row = 16 * w4 + n16;
     char* xd = xs + sl * XSLOT + w4 * NX * 1024;
-    if (P.xdma) {
+    if constexpr (XV) {
 #pragma unroll
       for (int c = 0; c < NX; ++c) {
         const int j = 32 * kb + 8 * gq + 4 * c;
@@ -202,8 +204,20 @@ __global__ void __launch_bounds__(kThreads1, 1) prefill_p1(PrefillParams P) {
             xr, (lds_ptr)(xd + c * 1024), 16,
             valid && j < d_in ? static_cast<uint32_t>(row * d_in + j) * static_cast<uint32_t>(ex) : kOob, 0, 0, 0);
       }
+    } else if (P.xdma == 2) {
+      // the same fragment a dword a lane: load d fills lane group d, lane l of
+      // it dword l % 4 of row l / 4
+#pragma unroll
+      for (int c = 0; c < NX; ++c)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          const int j = 32 * kb + 8 * d + (ACT == kDtF32 ? 4 * c + (lane & 3) : 2 * (lane & 3));
+          const uint32_t off = static_cast<uint32_t>((16 * w4 + (lane >> 2)) * d_in + j) * static_cast<uint32_t>(ex);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_ptr)(xd + c * 1024 + d * 256), 4,
+                                                   valid && j < d_in ? off : kOob, 0, 0, 0);
+        }
     } else {
-      // element loads (rows not whole 16-byte chunks), written in the same order
+      // element loads (rows of an odd number of 16-bit values), written in the same order
 #pragma unroll
       for (int c = 0; c < NX; ++c) {
         const int j = 32 * kb + 8 * gq + 4 * c;
@@ -272,7 +286,10 @@ __global__ void __launch_bounds__(kThreads1, 1) prefill_p1(PrefillParams P) {
     // round i has landed (each wave waits for its own loads, the barrier for
     // everyone's) and every wave is done with the slots of round i - 1
     asm volatile("" ::: "memory");  // round i - 1's LDS reads stay above the barrier
-    wait_vm_lds<(RR - 2) * (NX + NV)>();
+    if (!XV && P.xdma == 2)
+      wait_vm_lds<(RR - 2) * (4 * NX + NV)>();
+    else
+      wait_vm_lds<(RR - 2) * (NX + NV)>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     const int n = kSplit1 * i + grp;
@@ -888,18 +905,19 @@ hipError_t raise_lds_limit(K* fn, size_t bytes, std::atomic<size_t>& limit) {
   return hipSuccess;
 }
 
-template <int MS, int ACT, int SC, bool VW>
+template <int MS, int ACT, int SC, bool VW, bool XV>
 hipError_t launch_p1v(const PrefillParams& P, const PrefillGeom& g, hipStream_t stream) {
   static std::atomic<size_t> limit{65536};
-  hipError_t e = raise_lds_limit(&prefill_p1<MS, ACT, SC, VW>, g.smem1, limit);
+  hipError_t e = raise_lds_limit(&prefill_p1<MS, ACT, SC, VW, XV>, g.smem1, limit);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((prefill_p1<MS, ACT, SC, VW>), dim3(g.n_tt * g.n_lt * g.ks), dim3(kThreads1), g.smem1, stream,
+  hipLaunchKernelGGL((prefill_p1<MS, ACT, SC, VW, XV>), dim3(g.n_tt * g.n_lt * g.ks), dim3(kThreads1), g.smem1, stream,
                      P);
   return hipGetLastError();
 }
 template <int MS, int ACT, int SC>
 hipError_t launch_p1(const PrefillParams& P, const PrefillGeom& g, hipStream_t stream) {
-  return P.vw ? launch_p1v<MS, ACT, SC, true>(P, g, stream) : launch_p1v<MS, ACT, SC, false>(P, g, stream);
+  if (P.xdma != 1) return launch_p1v<MS, ACT, SC, false, false>(P, g, stream);
+  return P.vw ? launch_p1v<MS, ACT, SC, true, true>(P, g, stream) : launch_p1v<MS, ACT, SC, false, true>(P, g, stream);
 }
 
 template <int ACT, int SC, bool FAST>
@@ -1099,8 +1117,12 @@ namespace {
 PrefillParams prefill_params(const ForwardArgs& a, PrefillGeom& g) {
   const int64_t ex = a.act_dt == kDtF32 ? 4 : 2, es = a.sc_dt == kDtF32 ? 4 : 2;
   auto al = [](const void* q, int64_t n) { return reinterpret_cast<uintptr_t>(q) % n == 0; };
+  // global-to-LDS x loads: 16-byte aligned rows of whole 16-byte chunks, else
+  // whole dwords (a 4100-input f16 layer at 777 tokens: P1 took 29.7 us with
+  // element loads through registers, 24 with dwords)
+  const int xdma = al(a.x, 16) && (a.d_in * ex) % 16 == 0 ? 1 : (al(a.x, 4) && (a.d_in * ex) % 4 == 0 ? 2 : 0);
   // 16-byte V-word loads: whole 4-word groups per latent block row
-  const bool vw = a.r % 4 == 0 && al(a.V[0], 16) && al(a.V[1], 16);
+  const bool vw = xdma == 1 && a.r % 4 == 0 && al(a.V[0], 16) && al(a.V[1], 16);
   // P2 fast path: whole 4-output groups, 16-byte aligned U words, aligned h and y
   const bool fast = a.d_out % 4 == 0 && al(a.U[0], 16) && al(a.U[1], 16) && al(a.h[0], 4 * es) &&
                     al(a.h[1], 4 * es) && al(a.y, 4 * ex);
@@ -1134,8 +1156,7 @@ PrefillParams prefill_params(const ForwardArgs& a, PrefillGeom& g) {
   P.n_tt2 = g.n_tt2;
   P.res = g.res;
   P.kbc = g.kbc;
-  // global-to-LDS x loads need 16-byte aligned rows of whole 16-byte chunks
-  P.xdma = al(a.x, 16) && (a.d_in * ex) % 16 == 0;
+  P.xdma = xdma;
   P.vw = vw;
   P.fast = fast;
   P.wdp = p2_wdp(g, fast);

@@ -417,3 +417,18 @@ def test_few_tokens_many_and_shared_workspace():
     torch.cuda.synchronize()
     for y, z in zip(alone, many):
         assert torch.equal(y, z)
+
+
+# prefill stage 1: x rows of whole 16-byte chunks, of whole dwords only (d_in a multiple of 2, or any in fp32; x itself 4-byte
+# but not 16-byte aligned) and of neither, with tails of the last 32-input step
+@pytest.mark.parametrize("d_in", [64, 66, 94, 999, 1000, 4100])
+@pytest.mark.parametrize("act,sc", [("bf16", "f16"), ("f32", "f32"), ("f16", "bf16")])
+def test_prefill_row_alignment(d_in, act, sc):
+    li = synth.make_linear(d_in, 130, 50, 70, act_dtype=act, scale_dtype=sc, cfg=93, linear=d_in, l_over_sqrt_r=True)
+    _check(li, _run(li, "prefill"), label=f"{d_in} {act}/{sc}")
+    x, paths, _ = U.to_device(li, True)
+    buf = torch.full((x.numel() + 2,), float("nan"), dtype=x.dtype, device="cuda")
+    xs = buf[2:].view(x.shape) if act != "f32" else buf[1:-1].view(x.shape)
+    xs.copy_(x)
+    y = lb.lb_linear_forward(xs, paths, li.r, kernel=KERNELS["prefill"])
+    assert torch.equal(y, lb.lb_linear_forward(x, paths, li.r, kernel=KERNELS["prefill"]))
