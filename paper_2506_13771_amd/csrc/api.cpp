@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "lb_backward.h"
+#include "lb_few.h"
 #include "lb_latent.h"
 
 namespace {

@@ -171,17 +171,6 @@ __device__ __forceinline__ void st(void* p, int64_t i, float v) {
   }
 }
 
-// the bits st<DT> would store (16-bit dtypes)
-template <int DT>
-__device__ __forceinline__ uint32_t round16(float v) {
-  if constexpr (DT == kDtBF16) {
-    return f32_to_bf16_bits(v);
-  } else {
-    asm volatile("" : "+v"(v));  // the fp32 value is formed first, as in st<>
-    return __half_as_ushort(__float2half_rn(v));
-  }
-}
-
 // ---------------------------------------------------------------------------
 // buffer loads: 32-bit byte offsets into a buffer of known size; a read past
 // the end returns zero, so absent rows, columns and blocks need no clamping

@@ -230,12 +230,6 @@ bool stream_mma_supports(const ForwardArgs& a);
 size_t stream_mma_workspace_bytes(const ForwardArgs* a, int n);
 hipError_t stream_mma_init(const ForwardArgs* a, int n, uint64_t fingerprint, void* ws, hipStream_t stream);
 hipError_t stream_mma_forward(const ForwardArgs* a, int n, uint64_t fingerprint, void* ws, hipStream_t stream);
-// Linears of up to 64 tokens by the list's matrix-core stages, each in the
-// first ws_bytes (what lb_forward_workspace_bytes says) of its own workspace; n
-// (1 .. kFewMaxBatch) of one token tile count and one pair of dtypes at once.
-constexpr int kFewMaxBatch = 8;
-bool few_tokens_supports(const ForwardArgs& a, size_t ws_bytes);
-hipError_t launch_few_tokens(const ForwardArgs* a, const size_t* ws_bytes, int n, hipStream_t stream);
 size_t stream_workspace_bytes(const ForwardArgs* a, int n);
 hipError_t stream_init(const ForwardArgs* a, int n, uint64_t fingerprint, void* ws, hipStream_t stream);
 hipError_t stream_forward(const ForwardArgs* a, int n, uint64_t fingerprint, void* ws, hipStream_t stream);

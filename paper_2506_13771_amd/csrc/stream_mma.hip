@@ -29,6 +29,7 @@
 #include <vector>
 
 #include "device_common.h"
+#include "lb_few.h"
 #include "stream_plan.h"
 
 namespace lb {
@@ -473,6 +474,17 @@ __global__ void __launch_bounds__(kThreads) sm_r_kernel(const uint32_t* __restri
   if (!plan_ok(hdr, fp)) return;
   const uint32_t code = map[blockIdx.x];
   sm_r_body<NW, SC, false>(descs[code >> 16], static_cast<int>(code & 0xffffu) * kThreads + threadIdx.x);
+}
+
+// the bits st<DT> would store (16-bit dtypes)
+template <int DT>
+__device__ __forceinline__ uint32_t round16(float v) {
+  if constexpr (DT == kDtBF16) {
+    return f32_to_bf16_bits(v);
+  } else {
+    asm volatile("" : "+v"(v));  // the fp32 value is formed first, as in st<>
+    return __half_as_ushort(__float2half_rn(v));
+  }
 }
 
 // ---------------------------------------------------------------------------
