@@ -329,6 +329,11 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
       }
     }
   };
+  // fp32 inputs: the sums of kFold blocks are added apart, so that a run of 64
+  // blocks does not add 576 products' rounding to one accumulator (a list at 5.9e-7
+  // of the 64-bit result instead of 4.6e-7; 16-bit outputs round far above that)
+  constexpr int kFold = ACT == kDtF32 && !ONE ? (TT == 1 ? 4 : (TT == 2 ? 8 : 16)) : 0;
+  floatx4 tot[kFold > 0 ? MT * TT : 1] = {};
   constexpr int kAhead = kBuf - 2;  // chunks still in flight when one is used
   int buf = 0;
   for (int ch = 0; ch < nch; ++ch) {
@@ -349,7 +354,18 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
       }
     }
     buf = buf == kBuf - 1 ? 0 : buf + 1;
+    if constexpr (kFold > 0)
+      if ((ch + 1) % (kFold / CB) == 0) {
+#pragma unroll
+        for (int m = 0; m < MT * TT; ++m) {
+          tot[m] += acc[m / TT][m % TT];
+          acc[m / TT][m % TT] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
   }
+  if constexpr (kFold > 0)
+#pragma unroll
+    for (int m = 0; m < MT * TT; ++m) acc[m / TT][m % TT] += tot[m];
   // global-to-LDS loads past the run are still in flight: none may land after
   // the workgroup's LDS is given away
   __builtin_amdgcn_s_waitcnt(0);
