@@ -137,7 +137,9 @@ lb_status lb_pack_signs(const void* src, lb_dtype src_dtype, int64_t rows, int64
    (covers every kernel choice).  The workspace must be zero-filled once before
    its first use (lb_workspace_init does it); every call leaves it ready for
    the next one, so a workspace is reused without clearing, across calls of
-   any shape.  The decode kernel tags its intermediate values with a 32-bit
+   any shape and lists (lb_linear_forward_many).  Its first 4352 bytes hold the
+   control block and the counters of list launches, intermediate values come
+   after them.  The decode kernel tags its intermediate values with a 32-bit
    call counter kept in the workspace; a value left unread for exactly 2^32
    calls could be mistaken for a fresh one.  Calls that may run concurrently
    need distinct workspaces. */
@@ -188,7 +190,7 @@ lb_status lb_linear_forward(const void* x, lb_dtype act_dtype, int64_t T, int64_
    lb_noalloc_scratch_bytes() = 32 MiB per GPU, one copy per device, held until
    the process ends; the call allocates nothing (no hipMalloc, no allocating
    library routine).  Sizes whose lb_forward_workspace_bytes exceed the
-   scratch return LB_ERR_WORKSPACE; other checks and results as for
+   scratch and the 4096 bytes of list counters return LB_ERR_WORKSPACE; other checks and results as for
    lb_linear_forward (bit-identical to it).  The first call on a device
    resolves that device's copy and enqueues its zero fill on `stream`; that
    first call must not be captured in a graph (LB_ERR_ARG), later ones may be.

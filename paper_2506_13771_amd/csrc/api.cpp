@@ -300,8 +300,10 @@ namespace {
 // name as an address: each device's copy is resolved once with
 // hipGetSymbolAddress (that device current) and that pointer is what the
 // kernels get.
+// kNoAllocScratchBytes count the control block but not the counter lines after it.
 constexpr size_t kNoAllocScratchBytes = size_t(32) << 20;
-__device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+constexpr size_t kNoAllocBytes = kNoAllocScratchBytes + lb::kScratchOff - lb::kCtrlBytes;
+__device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 constexpr int kMaxDevices = 64;
 struct ScratchSlot {
@@ -326,7 +328,7 @@ lb_status scratch_for_current_device(hipStream_t stream, void** out) {
     if (cs != hipStreamCaptureStatusNone) return LB_ERR_ARG;
     void* ptr = nullptr;
     if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || ptr == nullptr) return LB_ERR_HIP;
-    if (lb::launch_fill_zero(ptr, kNoAllocScratchBytes, stream) != hipSuccess) return LB_ERR_HIP;
+    if (lb::launch_fill_zero(ptr, kNoAllocBytes, stream) != hipSuccess) return LB_ERR_HIP;
     s.ptr = ptr;
     s.ready = true;
   }
@@ -346,7 +348,7 @@ lb_status lb_linear_forward_noalloc(const void* x, lb_dtype act_dtype, int64_t T
   if (!dtype_ok(act_dtype) || !dtype_ok(scale_dtype)) return LB_ERR_DTYPE;
   const lb_status st = check_sizes(T, d_in, d_out, r);
   if (st != LB_OK) return st;
-  if (lb_forward_workspace_bytes(T, d_in, d_out, r) > kNoAllocScratchBytes) return LB_ERR_WORKSPACE;
+  if (lb_forward_workspace_bytes(T, d_in, d_out, r) > kNoAllocBytes) return LB_ERR_WORKSPACE;
   if (T == 0 || d_out == 0) return LB_OK;
   if (!y || (d_in > 0 && !x)) return LB_ERR_NULL;
   if (!aligned(x, dtype_size(act_dtype)) || !aligned(y, dtype_size(act_dtype))) return LB_ERR_ALIGN;
@@ -355,7 +357,7 @@ lb_status lb_linear_forward_noalloc(const void* x, lb_dtype act_dtype, int64_t T
   void* ws = nullptr;
   const lb_status ss = scratch_for_current_device(stream, &ws);
   if (ss != LB_OK) return ss;
-  return lb_linear_forward_kernel(x, act_dtype, T, d_in, d_out, r, paths, scale_dtype, y, ws, kNoAllocScratchBytes,
+  return lb_linear_forward_kernel(x, act_dtype, T, d_in, d_out, r, paths, scale_dtype, y, ws, kNoAllocBytes,
                                   LB_KERNEL_AUTO, stream);
 }
 

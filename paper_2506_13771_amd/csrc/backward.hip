@@ -442,7 +442,7 @@ BackwardLayout backward_layout(int T, int d_in, int d_out, int r) {
   if (s3 > stage) stage = s3;
   const GemmGeom gu = gemm_geom(T, d_out, r), gv = gemm_geom(T, d_in, r);
   const size_t part = align256(4 * (gu.part_floats > gv.part_floats ? gu.part_floats : gv.part_floats));
-  L.z_off = kCtrlBytes;
+  L.z_off = kScratchOff;
   L.dw_off = L.z_off + lat;
   L.stage_off = L.dw_off + lat;
   L.stage2_off = L.stage_off + align256(stage);

@@ -686,11 +686,11 @@ DecodeGeom decode_geometry(int T, int d_in, int d_out, int r) {
   const size_t s2 = 4 * tch * per_tok;
   g.smem_bytes = s1 > s2 ? s1 : s2;
   g.smem_bytes_elem = s1e > s2 ? s1e : s2;
-  g.partial_off = kCtrlBytes;
+  g.partial_off = kScratchOff;
   g.partial_slots = static_cast<size_t>(2) * g.s1d * T * r;
   g.wbuf_off = g.partial_off + align256(8 * g.partial_slots);
   g.wbuf_slots = g.direct ? 0 : static_cast<size_t>(2) * T * r;
-  g.ws_bytes = g.wbuf_off + align256(8 * g.wbuf_slots);
+  g.ws_bytes = g.partial_slots ? g.wbuf_off + align256(8 * g.wbuf_slots) : kCtrlBytes;
   return g;
 }
 

@@ -614,11 +614,11 @@ MmaGeom decode_mma_geometry(int T, int d_in, int d_out, int r, int act_dt) {
   const size_t s1_lds = static_cast<size_t>(kWaves) * 4 * 64 * 16;
   const size_t s2_lds = 4 * (2 * nkb * 64 + 2 * tch * 32 * nkb + (nsrc > 1 ? 2 * tch * nsrc * r : 0));
   g.smem_bytes = s1_lds > s2_lds ? s1_lds : s2_lds;
-  g.partial_off = kCtrlBytes;
+  g.partial_off = kScratchOff;
   g.partial_slots = static_cast<size_t>(2) * g.s1d * T * r;
   g.wbuf_off = g.partial_off + align256(8 * g.partial_slots);
   g.wbuf_slots = g.direct ? 0 : static_cast<size_t>(2) * T * r;
-  g.ws_bytes = g.wbuf_off + align256(8 * g.wbuf_slots);
+  g.ws_bytes = g.partial_slots ? g.wbuf_off + align256(8 * g.wbuf_slots) : kCtrlBytes;
   return g;
 }
 

@@ -110,6 +110,17 @@ constexpr int kCtrlError = 2;      // set to nonzero if a bounded wait expired
 constexpr int kCtrlWords = 64;
 constexpr size_t kCtrlBytes = ((kCtrlWords * 4 + 255) / 256) * 256;
 
+// After the control block, a list launch's counters: one per member, of its
+// finished stage-2 workgroups, in a 256-byte line of its own (atomics on one
+// line serialise).  They are zero between calls, so no call keeps anything else
+// there: intermediate values of every call start at kScratchOff of its
+// workspace, also of the calls that use no counters, since a workspace serves
+// lists and single calls in turn.
+constexpr int kDecodeMaxBatch = 16;  // linears per list launch of a single-launch decode kernel
+constexpr size_t kListCtrStride = 256;
+constexpr size_t kListHdrBytes = kCtrlBytes + kDecodeMaxBatch * kListCtrStride;
+constexpr size_t kScratchOff = kListHdrBytes;
+
 // ---------------------------------------------------------------------------
 // kernel launchers (defined in the .hip files)
 // ---------------------------------------------------------------------------
@@ -152,13 +163,7 @@ struct DecodeGeom {
 DecodeGeom decode_geometry(int T, int d_in, int d_out, int r);
 bool decode_supports(int64_t T, int64_t d_in, int64_t d_out, int64_t r);
 constexpr int kDecodeMaxTokens = 4;
-constexpr int kDecodeMaxBatch = 16;  // linears per list launch of the look-up-table decode kernel
 constexpr int kDecodeMaxRank = 1024;  // stage-2 tables of one token fit in LDS
-// Workspace of lb_linear_forward_many: the list's control block, then one
-// counter of finished stage-2 workgroups per member of a list launch, each in
-// a 256-byte line of its own (atomics on one line serialise), then the slices.
-constexpr size_t kListCtrStride = 256;
-constexpr size_t kListHdrBytes = kCtrlBytes + kDecodeMaxBatch * kListCtrStride;
 
 // Matrix-core decode kernel geometry.
 struct MmaGeom {

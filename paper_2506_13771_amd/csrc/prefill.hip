@@ -1093,7 +1093,7 @@ PrefillGeom prefill_geometry(int T, int d_in, int d_out, int r) {
   plan_lds(g, kDtF32, kDtF32, false, false);
   // workspace (nothing beyond the control block when there is nothing to compute)
   const bool work = T > 0 && d_in > 0 && r > 0;
-  g.pbuf_off = kCtrlBytes;
+  g.pbuf_off = work ? kScratchOff : kCtrlBytes;
   g.pbuf_floats = work ? static_cast<size_t>(g.ks) * g.n_tt * 2 * g.ns16p * kPart : 0;
   g.wterm_off = g.pbuf_off + align256(4 * g.pbuf_floats);
   g.wterm_bytes = work ? static_cast<size_t>(2) * 3 * g.nkb * T * 64 : 0;
@@ -1202,7 +1202,7 @@ size_t latent_workspace_bytes(int T, int d_in, int r) {
 
 size_t from_latent_workspace_bytes(int T, int r) {
   const PrefillGeom g = prefill_geometry(T, kNoStage1, 0, r);
-  return kCtrlBytes + align256(g.wterm_bytes);
+  return g.wterm_bytes ? kScratchOff + align256(g.wterm_bytes) : kCtrlBytes;
 }
 
 hipError_t launch_latent(const ForwardArgs& a, int lat_dt, hipStream_t stream) {
@@ -1260,7 +1260,7 @@ hipError_t launch_stage2_scaled(const ForwardArgs& a, const float* w, hipStream_
 
 hipError_t launch_from_latent(const ForwardArgs& a, const void* lat, int lat_dt, hipStream_t stream) {
   PrefillGeom g = prefill_geometry(a.T, kNoStage1, a.d_out, a.r);
-  g.wterm_off = kCtrlBytes;  // no partial sums
+  g.wterm_off = kScratchOff;  // no partial sums
   PrefillParams P = prefill_params(a, g);
   P.lat = const_cast<void*>(lat);
   switch (a.act_dt) {

@@ -973,7 +973,7 @@ constexpr int one_max_cls(int tt) { return tt == 1 ? 3 : (tt == 2 ? 2 : 1); }
 SmGeom one_geometry(const ForwardArgs& a, size_t ws_bytes) {
   SmGeom g = sm_geometry(a, kMaxBpr);
   const int nbt = nblocks32(a.d_in);
-  const size_t room = ws_bytes - kCtrlBytes;
+  const size_t room = ws_bytes - kScratchOff;
   const size_t frag = align256(frag_bytes(a.T, a.r, nw_of(a.act_dt)));
   const int max_runs = std::max(1, std::min(kOneMaxRuns, nbt / kOneMinBpr));
   int c = one_max_cls(g.tt);
@@ -1059,7 +1059,7 @@ hipError_t one_sc(int sc_dt, const FewArgs& A, int n, int tt, int c, int n1, int
 }  // namespace
 
 bool few_tokens_supports(const ForwardArgs& a, size_t ws_bytes) {
-  return stream_mma_supports(a) && has_work(a) && ws_bytes > kCtrlBytes && one_geometry(a, ws_bytes).bpr > 0;
+  return stream_mma_supports(a) && has_work(a) && ws_bytes > kScratchOff && one_geometry(a, ws_bytes).bpr > 0;
 }
 
 hipError_t launch_few_tokens(const ForwardArgs* a, const size_t* ws_bytes, int n, hipStream_t stream) {
@@ -1072,7 +1072,7 @@ hipError_t launch_few_tokens(const ForwardArgs* a, const size_t* ws_bytes, int n
     const SmGeom g = one_geometry(a[i], ws_bytes[i]);
     StreamLinear& L = A.l[i];
     fill_desc(L, a[i], g);
-    char* data = static_cast<char*>(a[i].ws) + kCtrlBytes;
+    char* data = static_cast<char*>(a[i].ws) + kScratchOff;
     L.part = reinterpret_cast<float*>(data);
     L.wlat = reinterpret_cast<float*>(data + align256(part_bytes(g)));
     c = std::max(c, g.cls % kMtClasses);

@@ -224,3 +224,27 @@ def test_workspace_status_after_calls():
     _, ws2 = _many(lins)
     assert lb.lb_workspace_status(ws2) == 0
     assert lb.lb_workspace_status(ws2) == 0
+
+
+@pytest.mark.parametrize("one", [(1, 4096, 4096, 80), (16, 4096, 4096, 80), (8, 1024, 1024, 80), (100, 512, 512, 80)],
+                         ids=["lut", "few", "mma", "prefill"])
+def test_many_after_a_single_call_on_its_workspace(one):
+    """A list launch counts its members' workgroups on words of its workspace that must still be
+    zero after a single call of any kernel used it; with other values there the launch did not
+    end its call, and the next one on the workspace took its values for its own."""
+    single = _linears([one + ("bf16", "f16")], cfg=30)[0]
+    lins = _linears([(1, 4096, 4096, 80, "bf16", "f16"), (1, 4096, 1024, 80, "bf16", "f16"),
+                     (1, 2048, 512, 64, "bf16", "f16")], cfg=31)
+    arr, _ = lb.make_descs([(x, paths, li.r, None) for li, x, paths in lins])
+    need = max(lb.lb_forward_many_workspace_bytes(arr, len(lins)), lb.lb_forward_workspace_bytes(*one))
+    ws = lb.lb_workspace_init(torch.empty(need, dtype=torch.uint8, device="cuda"))
+    g = torch.Generator(device="cuda").manual_seed(30)
+    for rep in range(3):
+        lb.lb_linear_forward(single[1], single[2], single[0].r, workspace=ws)
+        for _ in range(2):
+            for _, x, _ in lins:
+                x.copy_(torch.randn(x.shape, generator=g, device="cuda").to(x.dtype))
+            ys, _ = _many(lins, ws=ws)
+            for i, (y, z) in enumerate(zip(ys, _singles(lins))):
+                assert _same_bits(y, z), (rep, i)
+    assert lb.lb_workspace_status(ws) == 0
