@@ -139,10 +139,13 @@ lb_status lb_pack_signs(const void* src, lb_dtype src_dtype, int64_t rows, int64
    the next one, so a workspace is reused without clearing, across calls of
    any shape and lists (lb_linear_forward_many).  Its first 4352 bytes hold the
    control block and the counters of list launches, intermediate values come
-   after them.  The decode kernel tags its intermediate values with a 32-bit
-   call counter kept in the workspace; a value left unread for exactly 2^32
-   calls could be mistaken for a fresh one.  Calls that may run concurrently
-   need distinct workspaces. */
+   after them.  The decode kernels tag their intermediate values with a call counter
+   kept in the workspace, in bit patterns that no other intermediate value has.
+   The tags repeat after 4128768 decode calls; until then a call clears the old ones
+   from the bytes it is given as the workspace, so pass the workspace's whole size
+   (beyond the bytes given to that call, a value left unread for exactly
+   4128768 calls could be mistaken for a fresh one).  Calls that may run
+   concurrently need distinct workspaces. */
 size_t lb_forward_workspace_bytes(int64_t T, int64_t d_in, int64_t d_out, int64_t r);
 
 /* Zero-fill a workspace of `bytes` bytes on `stream`. */

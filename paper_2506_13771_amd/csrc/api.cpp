@@ -505,7 +505,8 @@ lb_status lb_linear_forward_many(const lb_linear_desc* descs, int64_t n, void* w
       bk = k;
       batch[nb] = make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, ws + off, sb);
       // one control block for the whole list: the start of its workspace
-      batch[nb++].ctrl = workspace;
+      batch[nb].ctrl = workspace;
+      batch[nb++].ctrl_bytes = workspace_bytes;
     } else {
       const lb_status st = lb_linear_forward_kernel(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths,
                                                     d.scale_dtype, d.y, ws + off, sb, LB_KERNEL_AUTO, stream);

@@ -44,10 +44,12 @@
 //  * Waits only ever target workgroups with lower block ids, which are
 //    dispatched earlier on every XCD, so the grid cannot deadlock; every wait
 //    is bounded and records an error word instead of hanging.
-//  * The tag is one more than a per-workspace epoch word; the last stage-2
-//    workgroup to finish (counted with one atomic per workgroup) stores it as
-//    the new epoch, so consecutive calls, graph replays included, never
-//    confuse each other's slots and the workspace needs no clearing.
+//  * The tag is that of a per-workspace epoch word (call_tag); the last stage-2
+//    workgroup to count itself (one atomic per workgroup) moves the word on, so
+//    consecutive calls, graph replays included, never confuse each other's slots
+//    and the workspace needs no clearing between calls.  No other call's
+//    intermediate values look like a tag, and tags are cleared from the
+//    workspace before they come round again (end_call).
 #include <atomic>
 #include <type_traits>
 
@@ -86,6 +88,7 @@ struct DecodeParams {
   uint32_t* ctrl;
   uint64_t* partial;  // [2][T][s1d][r] tagged partial l (.) z of each run
   uint64_t* wbuf;     // [2][T][r]      tagged l (.) z (two-level mode)
+  SlotSpan span;      // where the slots end
   int T, d_in, d_out, r;
   int nkt;     // 16-latent tiles per path
   int s1d;     // d_in runs per tile
@@ -187,7 +190,7 @@ __device__ void stage1(const DecodeParams& P, int wg, float* smem) {
     if (lane < 16) red[(wave * TM + t) * 16 + lane] = v;
   }
   pin(epoch);
-  const uint32_t tag = epoch + 1u;  // this call's tag: one more than the epoch the previous call left
+  const uint32_t tag = call_tag(epoch);  // this call's tag, by the epoch the previous call left
   __syncthreads();
   if (tid < 16 * TM) {
     const int t = tid >> 4;  // tid & 15 == kk: this thread loaded l of its own column
@@ -301,7 +304,7 @@ __device__ void stage2(const DecodeParams& P, int q2, float* smem) {
       }
       if (t0 == 0) {
         pin(epoch);
-        tag = epoch + 1u;
+        tag = call_tag(epoch);
         // count this workgroup as one that has read the epoch (the returned
         // count is used at the end)
         if (tid == 0) done_before = atomic_add_relaxed(P.ctr, 1u);
@@ -373,7 +376,7 @@ __device__ void stage2(const DecodeParams& P, int q2, float* smem) {
       }
       if (t0 == 0 && e0 == 0) {
         pin(epoch);
-        tag = epoch + 1u;
+        tag = call_tag(epoch);
         // count this workgroup as one that has read the epoch (the returned
         // count is used at the end)
         if (tid == 0) done_before = atomic_add_relaxed(P.ctr, 1u);
@@ -452,23 +455,16 @@ __device__ void stage2(const DecodeParams& P, int q2, float* smem) {
   }
   if (!ok) atomic_store_relaxed(P.ctrl + kCtrlError, 1u);
 
-  // The last stage-2 workgroup to count itself stores the tag as the epoch
-  // for the next call.  Every workgroup of this call has read the epoch by
+  // The last stage-2 workgroup to count itself moves the epoch on for the
+  // next call.  Every workgroup of this call has read the epoch by
   // then: stage-2 workgroups counted themselves after reading it, and every
   // stage-1 workgroup published values carrying the tag, which this
   // workgroup has gathered (directly, or through the two-level reducers).
   // In a list launch each linear counts its workgroups on a word of its own
   // (one contended word for all of them would serialise the atomics), and the
   // last workgroup of each linear counts that linear on the shared word.
-  if (tid == 0 && done_before == static_cast<uint32_t>(P.n_s2 - 1)) {
-    atomic_store_relaxed(P.ctr, 0u);
-    const bool last = P.n_members <= 1 ||
-                      atomic_add_relaxed(P.ctrl + kCtrlDone, 1u) == static_cast<uint32_t>(P.n_members - 1);
-    if (last) {
-      if (P.n_members > 1) atomic_store_relaxed(P.ctrl + kCtrlDone, 0u);
-      atomic_store_relaxed(P.ctrl + kCtrlEpoch, tag);
-    }
-  }
+  if (tid < 64)
+    end_call(P.ctrl, P.ctr, epoch, P.n_members, tid == 0 && done_before == static_cast<uint32_t>(P.n_s2 - 1), P.span);
 }
 
 template <int TM, int ACT, int SC, bool VEC, int WPL, bool OWN>
@@ -720,6 +716,7 @@ bool decode_params(const ForwardArgs& a, const DecodeGeom& g, DecodeParams& P) {
   P.ctrl = reinterpret_cast<uint32_t*>(a.ctrl ? a.ctrl : a.ws);
   P.partial = reinterpret_cast<uint64_t*>(ws + g.partial_off);
   P.wbuf = reinterpret_cast<uint64_t*>(ws + g.wbuf_off);
+  P.span = slot_span(a, g.ws_bytes);
   P.T = a.T;
   P.d_in = a.d_in;
   P.d_out = a.d_out;

@@ -72,6 +72,7 @@ struct MmaParams {
   uint32_t* ctrl;
   uint64_t* partial;  // [2][T][s1d][r] tagged partial l (.) z
   uint64_t* wbuf;     // [2][T][r]      tagged l (.) z (two-level mode)
+  SlotSpan span;      // where the slots end
   int T, d_in, d_out, r;
   int nmf;     // 16-latent tiles per path
   int s1d;     // d_in runs per tile
@@ -248,7 +249,7 @@ __device__ __forceinline__ void mma_stage1(const MmaParams& P, int wg, float* sm
     const floatx4 a2 = red[(2 * TT + tt) * 64 + lane], a3 = red[(3 * TT + tt) * 64 + lane];
     const int t = 16 * tt + C.n16;
     pin(epoch);
-    const uint32_t tag = epoch + 1u;
+    const uint32_t tag = call_tag(epoch);
     const bool reducer = !P.direct && c == P.s1d - 1;
     float sv[4];
 #pragma unroll
@@ -331,7 +332,7 @@ __device__ __forceinline__ void mma_stage2(const MmaParams& P, int q, float* sme
     }
   uint32_t epoch = load_epoch<4>(P.ctrl);
   pin(epoch);
-  const uint32_t tag = epoch + 1u;
+  const uint32_t tag = call_tag(epoch);
   // count this workgroup as one that has read the epoch (used at the end)
   uint32_t done_before = 0u;
   if (tid == 0) done_before = atomic_add_relaxed(P.ctr, 1u);
@@ -460,23 +461,15 @@ __device__ __forceinline__ void mma_stage2(const MmaParams& P, int q, float* sme
     __syncthreads();  // the next chunk reuses the LDS
   }
   if (!ok) atomic_store_relaxed(P.ctrl + kCtrlError, 1u);
-  // The last stage-2 workgroup to count itself stores the tag as the next
-  // epoch.  Every workgroup of this call has read the epoch by then: stage-2
+  // The last stage-2 workgroup to count itself moves the epoch on.  Every workgroup of this call has read the epoch by then: stage-2
   // workgroups counted themselves after reading it, and every stage-1
   // workgroup published values carrying the tag, which this workgroup has
   // gathered (directly, or through the two-level reducers).
   // In a list launch each linear counts its workgroups on a word of its own
   // (one contended word for all of them would serialise the atomics), and the
   // last workgroup of each linear counts that linear on the shared word.
-  if (tid == 0 && done_before == static_cast<uint32_t>(P.n_s2 - 1)) {
-    atomic_store_relaxed(P.ctr, 0u);
-    const bool last = P.n_members <= 1 ||
-                      atomic_add_relaxed(P.ctrl + kCtrlDone, 1u) == static_cast<uint32_t>(P.n_members - 1);
-    if (last) {
-      if (P.n_members > 1) atomic_store_relaxed(P.ctrl + kCtrlDone, 0u);
-      atomic_store_relaxed(P.ctrl + kCtrlEpoch, tag);
-    }
-  }
+  if (wave == 0)
+    end_call(P.ctrl, P.ctr, epoch, P.n_members, tid == 0 && done_before == static_cast<uint32_t>(P.n_s2 - 1), P.span);
 }
 
 template <int TT, int ACT, int SC, bool VEC>
@@ -649,6 +642,7 @@ void mma_params(const ForwardArgs& a, const MmaGeom& g, MmaParams& P) {
   P.ctrl = reinterpret_cast<uint32_t*>(a.ctrl ? a.ctrl : a.ws);
   P.partial = reinterpret_cast<uint64_t*>(ws + g.partial_off);
   P.wbuf = reinterpret_cast<uint64_t*>(ws + g.wbuf_off);
+  P.span = slot_span(a, g.ws_bytes);
   P.T = a.T;
   P.d_in = a.d_in;
   P.d_out = a.d_out;

@@ -19,6 +19,7 @@ __device__ __forceinline__ void put_slot(uint64_t* p, uint32_t tag, float v) {
 __device__ __forceinline__ uint64_t get_slot(const uint64_t* p) {
   return __hip_atomic_load(const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ uint32_t call_tag(uint32_t epoch) { return kTagBase + epoch; }
 __device__ __forceinline__ float slot_value(uint64_t w) { return __uint_as_float(static_cast<uint32_t>(w)); }
 __device__ __forceinline__ bool slot_ready(uint64_t w, uint32_t tag) { return static_cast<uint32_t>(w >> 32) == tag; }
 
@@ -49,6 +50,62 @@ __device__ __forceinline__ bool gather_sum(const uint64_t* base, int64_t stride,
     if (c < n) s += slot_value(v[c]);
   sum = s;
   return true;
+}
+
+// Where a workspace's tagged slots may be, in units of 256 bytes from its
+// control block: this call's end, and the workspace's.
+struct SlotSpan {
+  uint32_t end, ws_end;
+};
+inline SlotSpan slot_span(const ForwardArgs& a, size_t slot_bytes) {
+  const char* ctrl = static_cast<const char*>(a.ctrl ? a.ctrl : a.ws);
+  const size_t ws = a.ctrl ? a.ctrl_bytes : a.ws_bytes;
+  const size_t end = static_cast<const char*>(a.ws) - ctrl + slot_bytes;
+  auto units = [](size_t b) { return static_cast<uint32_t>(b / 256 < 0xffffffffu ? b / 256 : 0xffffffffu); };
+  return SlotSpan{units(end + 255), units(ws)};
+}
+
+// The end of a call by its workgroup that was the last to count itself (wave 0
+// calls, lane 0 has ended): the epoch word moves on, and the first call of
+// either half of the tags clears the slots that carry a tag of the other half.
+// Slots of this call carry one of this half, and a slot is cleared only while
+// it still holds what was read, so workgroups still gathering are not
+// disturbed.  One wave does it, once in 2 million calls.
+__device__ __forceinline__ void clear_old_tags(uint32_t* ctrl, uint32_t epoch, uint32_t end) {
+  const uint32_t other = kTagBase + (epoch < kTagHalf ? kTagHalf : 0u);
+  const uint32_t n_other = epoch < kTagHalf ? kTagCount - kTagHalf : kTagHalf;
+  uint64_t* base = reinterpret_cast<uint64_t*>(ctrl);
+  const uint64_t n = static_cast<uint64_t>(end) * 32;  // slots from the control block
+  constexpr int kBatch = 8;
+  for (uint64_t i0 = kScratchOff / 8; i0 < n; i0 += 64 * kBatch) {
+    const uint64_t i = i0 + (threadIdx.x & 63);
+    uint64_t v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) v[u] = i + 64 * u < n ? get_slot(base + i + 64 * u) : 0u;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (i + 64 * u < n && static_cast<uint32_t>(v[u] >> 32) - other < n_other)
+        __hip_atomic_compare_exchange_strong(base + i + 64 * u, &v[u], uint64_t(0), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+// called by wave 0 of every stage-2 workgroup; `last` is set in lane 0 of the one
+// that ends its linear's part of the call
+__device__ __forceinline__ void end_call(uint32_t* ctrl, uint32_t* ctr, uint32_t epoch, int n_members, bool last,
+                                         const SlotSpan& span) {
+  uint32_t clear_end = 0;  // lane 0: slots before this are to be cleared
+  if (last) {
+    atomic_store_relaxed(ctr, 0u);
+    const bool all = n_members <= 1 || atomic_add_relaxed(ctrl + kCtrlDone, 1u) == static_cast<uint32_t>(n_members - 1);
+    if (all) {
+      if (n_members > 1) atomic_store_relaxed(ctrl + kCtrlDone, 0u);
+      atomic_store_relaxed(ctrl + kCtrlEpoch, epoch + 1u < kTagCount ? epoch + 1u : 0u);
+      if (epoch == 0u || epoch == kTagHalf) clear_end = min(atomic_load_relaxed(ctrl + kCtrlHigh), span.ws_end);
+    }
+    __hip_atomic_fetch_max(ctrl + kCtrlHigh, span.end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  clear_end = __builtin_amdgcn_readfirstlane(clear_end);
+  if (clear_end != 0u) clear_old_tags(ctrl, epoch, clear_end);
 }
 
 // ---------------------------------------------------------------------------

@@ -104,7 +104,7 @@ __device__ __forceinline__ bool spin_until_at_least(const uint32_t* p, uint32_t 
 // ---------------------------------------------------------------------------
 // workspace control block (fixed offsets at the start of every workspace)
 // ---------------------------------------------------------------------------
-constexpr int kCtrlEpoch = 0;      // decode: tag of the last completed call
+constexpr int kCtrlEpoch = 0;      // decode: completed calls, modulo kTagCount
 constexpr int kCtrlDone = 1;       // decode: finished stage-2 workgroups of the running call
 constexpr int kCtrlError = 2;      // set to nonzero if a bounded wait expired
 constexpr int kCtrlWords = 64;
@@ -120,6 +120,27 @@ constexpr int kDecodeMaxBatch = 16;  // linears per list launch of a single-laun
 constexpr size_t kListCtrStride = 256;
 constexpr size_t kListHdrBytes = kCtrlBytes + kDecodeMaxBatch * kListCtrStride;
 constexpr size_t kScratchOff = kListHdrBytes;
+// Word of the control block's workspace (in the first counter line, past its
+// counter) that holds the end of the tagged slots written so far, in units of
+// 256 bytes from the control block.
+constexpr int kCtrlHigh = static_cast<int>((kCtrlBytes + kListCtrStride / 2) / 4);
+
+// ---------------------------------------------------------------------------
+// tags of the single-launch kernels' slots (the high words of 64-bit slots; the
+// protocol is in device_common.h)
+//
+// Other calls leave fp32 partial sums and pairs of bf16 terms in the bytes of a
+// workspace where these kernels keep their slots, so a tag is a word that none
+// of those can be: a signalling NaN, which no arithmetic gives, and whose upper
+// half is not infinity's, which the upper one of two bf16 terms may be.
+// (A plain call counter met the bare bf16 patterns of a last latent block half
+// empty after some 15000 calls.)
+// ---------------------------------------------------------------------------
+constexpr uint32_t kTagBase = 0x7F810000u;             // tag of epoch e: kTagBase + e
+constexpr uint32_t kTagCount = 0x7FC00000u - kTagBase;  // epochs 0 .. kTagCount - 1
+// Half of the tags are in use while the other half is taken out of the workspace:
+// the first call of a half clears every slot that carries a tag of the other.
+constexpr uint32_t kTagHalf = kTagCount / 2;
 
 // ---------------------------------------------------------------------------
 // kernel launchers (defined in the .hip files)
@@ -140,8 +161,10 @@ struct ForwardArgs {
   // control block (epoch, done counter, error word) of the decode kernels'
   // call protocol; nullptr: the start of ws.  Every linear of a list launch
   // shares the control block at the start of the list's workspace, so that
-  // tags stay unique per workspace whatever the list's layout.
+  // tags stay unique per workspace whatever the list's layout; ctrl_bytes are
+  // the bytes of that workspace (without ctrl: ws_bytes).
   void* ctrl = nullptr;
+  size_t ctrl_bytes = 0;
 };
 
 // Look-up-table decode kernel geometry (pure function of the sizes; also sizes

@@ -432,3 +432,102 @@ def test_prefill_row_alignment(d_in, act, sc):
     xs.copy_(x)
     y = lb.lb_linear_forward(xs, paths, li.r, kernel=KERNELS["prefill"])
     assert torch.equal(y, lb.lb_linear_forward(x, paths, li.r, kernel=KERNELS["prefill"]))
+
+
+# ---------------------------------------------------------------------------
+# one workspace for calls that tag their intermediate values and calls that do not
+# ---------------------------------------------------------------------------
+TAG_BASE, TAG_COUNT = 0x7F810000, 0x3F0000  # tags of the decode kernels' slots, by epoch
+SCRATCH = 4352  # first byte of a workspace's intermediate values
+
+
+def _call(T, d_in, d_out, r, act="bf16", sc="f16", cfg=94):
+    li = synth.make_linear(d_in, d_out, r, T, act_dtype=act, scale_dtype=sc, cfg=cfg, linear=T + r, l_over_sqrt_r=True)
+    x, paths, _ = U.to_device(li, True)
+    return x, paths, r
+
+
+def _zeroed(*shapes):
+    n = max(lb.lb_forward_workspace_bytes(*s) for s in shapes)
+    return lb.lb_workspace_init(torch.empty(n, dtype=torch.uint8, device="cuda"))
+
+
+def _high_words(ws):
+    return ws[SCRATCH:].view(torch.int32)[1::2]
+
+
+def test_untagged_words_are_no_tags():
+    # r % 32 in 1..16: the upper halves of the last latent block's term pairs are zero, so whole words are bare bf16 patterns,
+    # which the call counter reaches after some 15000 decode calls
+    first, second = (16, 4096, 4096, 80), (15, 11008, 4096, 128)
+    a, b = _call(*first), _call(*second)
+    ref = lb.lb_linear_forward(b[0], b[1], b[2], kernel=KERNELS["mma"])
+    ws = _zeroed(first, second)
+    lb.lb_linear_forward(a[0], a[1], a[2], workspace=ws)
+    torch.cuda.synchronize()
+    left = ws.clone()
+    hi = _high_words(ws)
+    vals, counts = hi[(hi > 1) & (hi < 65536)].unique(return_counts=True)
+    assert len(vals) > 40
+    for v in vals[counts.argsort(descending=True)[:40]].tolist():
+        ws.copy_(left)
+        ws.view(torch.int32)[0] = v - 1
+        y = lb.lb_linear_forward(b[0], b[1], b[2], workspace=ws, kernel=KERNELS["mma"])
+        assert torch.equal(y, ref), v
+    assert lb.lb_workspace_status(ws) == 0
+
+
+@pytest.mark.parametrize("act,sc", [("bf16", "f16"), ("f16", "bf16"), ("f32", "f32")])
+@pytest.mark.parametrize("T", [16, 100])
+def test_intermediate_values_hold_no_tag(T, act, sc):
+    # the few-token and prefill stages on ordinary values, infinities, NaNs (of every kind: quiet, signalling, of either
+    # sign and with payloads) and values near the types' ends
+    shape = (T, 1024, 1024, 80)
+    x, paths, r = _call(*shape, act=act, sc=sc)
+    it, special = {"bf16": (torch.int16, [0x7F80, 0xFF80, 0x7FC0, 0xFFC0, 0x7F81, 0x7FBF, 0xFFA0, 0x7FFF, 0x7F7F, 1]),
+                   "f16": (torch.int16, [0x7C00, 0xFC00, 0x7E00, 0xFE00, 0x7C01, 0x7DFF, 0xFD00, 0x7FFF, 0x7BFF, 1]),
+                   "f32": (torch.int32, [0x7F800000, 0xFF800000, 0x7FC00000, 0xFFC00000, 0x7F810000, 0x7FBFFFFF,
+                                         0xFFA00000, 0x7FFFFFFF, 0x7F7FFFFF, 1])}[act]
+    wrap = 16 if it == torch.int16 else 32
+    ws = _zeroed(shape)
+    for fill in [None] + special:
+        xs = x.clone()
+        if fill is not None:
+            xs.view(it)[::3, 7] = fill - (1 << wrap) if fill >> (wrap - 1) else fill
+        ws[SCRATCH:].zero_()
+        lb.lb_linear_forward(xs, paths, r, workspace=ws)
+        hi = _high_words(ws)
+        assert int((hi != 0).sum()) > 1000
+        assert not bool(((hi >= TAG_BASE) & (hi < TAG_BASE + TAG_COUNT)).any()), fill
+
+
+@pytest.mark.parametrize("kernel,T", [("decode", 1), ("mma", 8)])
+def test_tags_come_round(kernel, T):
+    # the epoch word moves on to 0 after the last tag; the first call of each half takes the other half's tags out of the
+    # workspace, so a value left from a call with the same tag is not taken for a fresh one
+    big, small = (T, 4096, 1024, 144), (T, 512, 512, 80)
+    b, s = _call(*big), _call(*small)
+    ref_b, ref_s = (lb.lb_linear_forward(c[0], c[1], c[2], kernel=KERNELS[kernel]) for c in (b, s))
+    ws = _zeroed(big, small)
+    ctrl = ws.view(torch.int32)
+    half = TAG_COUNT // 2
+
+    def tags(lo, hi):
+        h = _high_words(ws)
+        return int(((h >= TAG_BASE + lo) & (h < TAG_BASE + hi)).sum())
+
+    x0 = b[0].clone()
+    for first, turn, after in ((5, half, half + 1), (half + 5, TAG_COUNT - 1, 1)):
+        b[0].copy_(-2 * x0)
+        ctrl[0] = first
+        lb.lb_linear_forward(b[0], b[1], b[2], workspace=ws, kernel=KERNELS[kernel])
+        assert int(ctrl[0]) == first + 1 and tags(first, first + 1) > 0
+        ctrl[0] = turn
+        for _ in range(2):
+            assert torch.equal(lb.lb_linear_forward(s[0], s[1], s[2], workspace=ws, kernel=KERNELS[kernel]), ref_s)
+        assert int(ctrl[0]) == (turn + 2) % TAG_COUNT == after + (1 if turn == half else 0)
+        assert (tags(0, half) if turn == half else tags(half, TAG_COUNT - 1)) == 0
+        b[0].copy_(x0)
+        ctrl[0] = first
+        assert torch.equal(lb.lb_linear_forward(b[0], b[1], b[2], workspace=ws, kernel=KERNELS[kernel]), ref_b)
+    assert lb.lb_workspace_status(ws) == 0
