@@ -120,19 +120,48 @@ lb_kernel auto_kernel(int64_t T, int64_t d_in, int64_t d_out, int64_t r) {
 }
 
 // Whether AUTO runs the three few-token stages (launch_few_tokens) for a,
-// which a kernel above takes, instead of it.  They need the aligned groups of
-// four of the matrix-core lists.  Against the kernel above, us per call on the
-// 7B, 13B and 70B shapes: 16 tokens 12-21 (17-42 matrix-core decode), 32 tokens
-// 12-24 (15-45 prefill), 64 tokens 14-32 (15-50), except past 48 tokens with
-// very many outputs, where prefill's larger output units win (8192 -> 28672, r =
-// 304: 28.4 against 27.5).  Below 16 tokens one launch beats three while r d_out
-// is small (8 tokens, 4096 -> 4096: r = 80 13.4 decode; 4096 -> 11008, r = 128
-// 15.0 against 16.8; 3 tokens, r = 544 18.0 against 23.0).
-bool prefer_few(const lb::ForwardArgs& a) {
-  if (a.T <= kAutoLutTokens || a.T > 64 || (a.T > 48 && a.d_out > 16384)) return false;
-  const int64_t rd = static_cast<int64_t>(a.r) * a.d_out;
-  if (a.T < 16 && !(a.T >= 8 && rd >= 1000000) && rd < 2000000) return false;
-  return lb::few_tokens_supports(a, lb_forward_workspace_bytes(a.T, a.d_in, a.d_out, a.r));
+// which a kernel above takes, instead of it; `need`: its workspace bytes.  They
+// need the aligned groups of four of the matrix-core lists.  us per call,
+// few-token stages against the kernel above:
+//   T < 8    4096 -> 4096: r = 544, T = 3 17.3 against 23.9; 28672 -> 8192, r = 304 21.1
+//            against 28.7.  They win from r (d_in + d_out) of about 2e6 (5120 ->
+//            13824, r = 160, T = 4: 14.4 against 16.4), but then a 13B block is split: its other
+//            linears stay on the decode kernel (5120 -> 5120, r = 112, T = 3 13.3
+//            against 12.0), and lb_linear_forward_many takes 38 us for both kinds of
+//            launch where one takes 23.  Hence 3.2e6, past a 13B block's largest.
+//   T < 16   4096 -> 4096, T = 8: r = 64 12.5 against 11.6, r = 80 12.7 against 13.7; 5120
+//            -> 5120, r = 112 13.3 against 17.2; narrower layers from more outputs on
+//            (2048 -> 16384, r = 64 12.2 against 12.7; 2048 -> 2048, r = 80 12.1 against 11.4,
+//            and a 2048-wide block stays whole).  The width keeps a 7B block whole:
+//            T = 8 in lb_linear_forward_many 22.7, split 34, all on the decode kernel 20.9.
+//   T < 32   r d_in decides, as stage 1 is what the decode kernel is slow at: T = 16 1024
+//            -> 1024, r = 80 11.6 against 11.3 and r = 48 11.6 against 10.8, 512 -> 512, r
+//            = 256 13.0 against 15.7; T = 20 512 -> 512, r = 32 13.3 against 11.9 and r = 64 13.5
+//            against 13.4, in fp32 17.0 against 12.8 and 17.1 against 15.2 (at these sizes the
+//            workspace holds one run of d_in up to T = 27), 1000 -> 1000, r = 40 14.0
+//            against 15.1; T = 31 1024 -> 1024, r = 16 12.4 against 13.5, fp32 14.5 against 13.4.
+//            (8192 -> 1024, r = 16, T = 16: 13.5 against 11.1, but 15.4 against 26 with the
+//            q of its block in one list.)
+//   T >= 32  against prefill: 384 -> 384, r = 32 12.8 against 11.6 and 512 -> 512, r = 32 12.2
+//            against 12.7 at T = 32, 256 -> 256, r = 32 in fp32 13.7 against 15.5 at T = 32 and
+//            17.6 against 16.4 at 64; 8192 -> 28672, r = 304, T = 64: 28.4 against 27.5
+//            (larger output units); fp32 16384 -> 4096, r = 100, T = 64: 38 against 33
+//            (x is read once per 16 or 48 latents), 13824 -> 5120, r = 224 37.3 against 39.1.
+bool prefer_few(const lb::ForwardArgs& a, size_t need) {
+  if (a.T <= kAutoLutTokens || a.T > 64) return false;
+  const int64_t rd_in = static_cast<int64_t>(a.r) * a.d_in, rd_out = static_cast<int64_t>(a.r) * a.d_out;
+  const bool f32 = a.act_dt == lb::kDtF32;
+  bool few;
+  if (a.T < 8)
+    few = rd_in + rd_out >= 3200000;
+  else if (a.T < 16)
+    few = rd_out >= 1000000 || (std::min(a.d_in, a.d_out) >= 4096 && rd_in + rd_out >= 600000);
+  else if (a.T < 32)
+    few = rd_in >= (a.T == 16 ? 75000 : (f32 ? (a.T < 28 ? 40000 : 20000) : (a.T < 24 ? 30000 : 15000)));
+  else
+    few = (rd_in >= 15000 || (f32 && a.T <= 48)) &&
+          !(a.T > 48 && (a.d_out > 16384 || (f32 && a.d_in >= 10000 && a.r <= 256)));
+  return few && lb::few_tokens_supports(a, need);
 }
 
 }  // namespace
@@ -269,7 +298,7 @@ lb_status lb_linear_forward_kernel(const void* x, lb_dtype act_dtype, int64_t T,
     // three on the matrix-core decode kernel, then the prefill kernels
     kernel = auto_kernel(T, d_in, d_out, r);
     if (kernel == LB_KERNEL_AUTO) return LB_ERR_SHAPE;
-    if (prefer_few(a)) {
+    if (prefer_few(a, need)) {
       e = lb::launch_few_tokens(&a, &need, 1, stream);
       return e == hipSuccess ? LB_OK : LB_ERR_HIP;
     }
@@ -386,7 +415,8 @@ bool auto_unsupported(const lb_linear_desc& d) {
 // a linear AUTO runs by the few-token stages
 bool runs_few(const lb_linear_desc& d) {
   return has_work(d) && auto_kernel(d.T, d.d_in, d.d_out, d.r) != LB_KERNEL_AUTO &&
-         prefer_few(make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, nullptr, 0));
+         prefer_few(make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, nullptr, 0),
+                    lb_forward_workspace_bytes(d.T, d.d_in, d.d_out, d.r));
 }
 
 // the list launch another linear joins: the look-up-table or the matrix-core

@@ -531,3 +531,30 @@ def test_tags_come_round(kernel, T):
         ctrl[0] = first
         assert torch.equal(lb.lb_linear_forward(b[0], b[1], b[2], workspace=ws, kernel=KERNELS[kernel]), ref_b)
     assert lb.lb_workspace_status(ws) == 0
+
+
+# AUTO's rule for 3 to 64 tokens, at both sides of each of its lines: the few-token stages, the kernel above them, or (None)
+# whatever a wide layer without aligned groups of four inputs takes.  Each kernel has bits of its own on these inputs, so the
+# one that ran is told by them.
+RULE = [(3, 5120, 13824, 160, "mma"), (3, 8192, 8192, 256, "few"), (7, 4096, 4096, 544, "few"), (7, 4096, 11008, 128, "mma"),
+        (8, 4096, 4096, 80, "few"), (8, 4096, 4096, 64, "mma"), (8, 2048, 2048, 80, "mma"), (8, 2048, 16384, 64, "few"),
+        (15, 4096, 1024, 128, "mma"), (15, 4096, 11008, 128, "few"), (16, 1024, 1024, 80, "few"), (16, 1024, 1024, 48, "mma"),
+        (16, 512, 2048, 64, "mma"), (17, 512, 512, 64, "few"), (23, 512, 512, 32, "mma"), (24, 512, 512, 32, "few"),
+        (31, 256, 256, 32, "mma"), (32, 512, 512, 32, "few"), (32, 384, 384, 32, "prefill"), (48, 1024, 16640, 64, "few"),
+        (49, 1024, 16640, 64, "prefill"), (64, 1024, 16384, 64, "few"), (20, 1022, 1024, 80, "mma"), (40, 1022, 1024, 80, "prefill")]
+RULE_F32 = [(24, 512, 512, 64, "mma"), (28, 512, 512, 64, "few"), (24, 1000, 1000, 40, "few"), (32, 384, 384, 32, "few"),
+            (49, 384, 384, 32, "prefill"), (64, 10240, 512, 256, "prefill"), (64, 10240, 512, 272, "few"),
+            (48, 10240, 512, 256, "few")]
+
+
+@pytest.mark.parametrize("case,act,sc", [(c, "bf16", "f16") for c in RULE] + [(c, "f32", "f32") for c in RULE_F32],
+                         ids=lambda v: f"T{v[0]}_{v[1]}x{v[2]}r{v[3]}" if isinstance(v, tuple) else v)
+def test_auto_rule(case, act, sc):
+    T, d_in, d_out, r, want = case
+    x, paths, _ = _call(T, d_in, d_out, r, act=act, sc=sc)
+    y = lb.lb_linear_forward(x, paths, r)
+    ran = [k for k in ("mma", "prefill") if torch.equal(y, lb.lb_linear_forward(x, paths, r, kernel=KERNELS[k]))]
+    # (16-bit outputs of two kernels may all agree where sums are short)
+    if want == "few":
+        ran = ran or ["few"]
+    assert want in ran, (ran, case)
