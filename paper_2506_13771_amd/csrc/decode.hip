@@ -211,6 +211,7 @@ __device__ void stage1(const DecodeParams& P, int wg, float* smem) {
       }
     }
   }
+  if (wg == 0 && tid == 0) note_slots(P.ctrl, P.span);
 }
 
 // ---------------------------------------------------------------------------

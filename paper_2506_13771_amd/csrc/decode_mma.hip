@@ -273,6 +273,7 @@ __device__ __forceinline__ void mma_stage1(const MmaParams& P, int wg, float* sm
     }
     if (!ok) atomic_store_relaxed(P.ctrl + kCtrlError, 1u);
   }
+  if (wg == 0 && tid == 0) note_slots(P.ctrl, P.span);
 }
 
 // ---------------------------------------------------------------------------

@@ -65,18 +65,17 @@ inline SlotSpan slot_span(const ForwardArgs& a, size_t slot_bytes) {
   return SlotSpan{units(end + 255), units(ws)};
 }
 
-// The end of a call by its workgroup that was the last to count itself (wave 0
-// calls, lane 0 has ended): the epoch word moves on, and the first call of
-// either half of the tags clears the slots that carry a tag of the other half.
-// Slots of this call carry one of this half, and a slot is cleared only while
-// it still holds what was read, so workgroups still gathering are not
-// disturbed.  One wave does it, once in 2 million calls.
+// Clears the slots before `end` (units of 256 bytes) that carry a tag of the half
+// the epoch is not in.  Slots of the running call carry one of the other half,
+// and a slot is cleared only while it still holds what was read, so workgroups
+// still publishing and gathering are not disturbed.  One wave does it, once in
+// 2 million calls.
 __device__ __forceinline__ void clear_old_tags(uint32_t* ctrl, uint32_t epoch, uint32_t end) {
   const uint32_t other = kTagBase + (epoch < kTagHalf ? kTagHalf : 0u);
-  const uint32_t n_other = epoch < kTagHalf ? kTagCount - kTagHalf : kTagHalf;
   uint64_t* base = reinterpret_cast<uint64_t*>(ctrl);
   const uint64_t n = static_cast<uint64_t>(end) * 32;  // slots from the control block
-  constexpr int kBatch = 8;
+  constexpr int kBatch = 4;
+#pragma unroll 1
   for (uint64_t i0 = kScratchOff / 8; i0 < n; i0 += 64 * kBatch) {
     const uint64_t i = i0 + (threadIdx.x & 63);
     uint64_t v[kBatch];
@@ -84,28 +83,32 @@ __device__ __forceinline__ void clear_old_tags(uint32_t* ctrl, uint32_t epoch, u
     for (int u = 0; u < kBatch; ++u) v[u] = i + 64 * u < n ? get_slot(base + i + 64 * u) : 0u;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
-      if (i + 64 * u < n && static_cast<uint32_t>(v[u] >> 32) - other < n_other)
+      if (i + 64 * u < n && static_cast<uint32_t>(v[u] >> 32) - other < kTagHalf)
         __hip_atomic_compare_exchange_strong(base + i + 64 * u, &v[u], uint64_t(0), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
   }
 }
-// called by wave 0 of every stage-2 workgroup; `last` is set in lane 0 of the one
-// that ends its linear's part of the call
+// Stage 1's first workgroup, one lane: the workspace's slots reach this far (not
+// at the end of the call, where the cold line would be waited for).
+__device__ __forceinline__ void note_slots(uint32_t* ctrl, const SlotSpan& span) {
+  __hip_atomic_fetch_max(ctrl + kCtrlHigh, span.end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The end of a call, by wave 0 of every stage-2 workgroup; `last` is set in lane
+// 0 of the one that was the last of its linear to count itself.
 __device__ __forceinline__ void end_call(uint32_t* ctrl, uint32_t* ctr, uint32_t epoch, int n_members, bool last,
                                          const SlotSpan& span) {
-  uint32_t clear_end = 0;  // lane 0: slots before this are to be cleared
+  bool all = false;
   if (last) {
     atomic_store_relaxed(ctr, 0u);
-    const bool all = n_members <= 1 || atomic_add_relaxed(ctrl + kCtrlDone, 1u) == static_cast<uint32_t>(n_members - 1);
+    all = n_members <= 1 || atomic_add_relaxed(ctrl + kCtrlDone, 1u) == static_cast<uint32_t>(n_members - 1);
     if (all) {
       if (n_members > 1) atomic_store_relaxed(ctrl + kCtrlDone, 0u);
       atomic_store_relaxed(ctrl + kCtrlEpoch, epoch + 1u < kTagCount ? epoch + 1u : 0u);
-      if (epoch == 0u || epoch == kTagHalf) clear_end = min(atomic_load_relaxed(ctrl + kCtrlHigh), span.ws_end);
     }
-    __hip_atomic_fetch_max(ctrl + kCtrlHigh, span.end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  clear_end = __builtin_amdgcn_readfirstlane(clear_end);
-  if (clear_end != 0u) clear_old_tags(ctrl, epoch, clear_end);
+  epoch = __builtin_amdgcn_readfirstlane(epoch);
+  if ((epoch == kTagClear || epoch == kTagClear + kTagHalf) && __builtin_amdgcn_readfirstlane(all))
+    clear_old_tags(ctrl, epoch, min(atomic_load_relaxed(ctrl + kCtrlHigh), span.ws_end));
 }
 
 // ---------------------------------------------------------------------------

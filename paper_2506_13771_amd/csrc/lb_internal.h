@@ -137,10 +137,13 @@ constexpr int kCtrlHigh = static_cast<int>((kCtrlBytes + kListCtrStride / 2) / 4
 // empty after some 15000 calls.)
 // ---------------------------------------------------------------------------
 constexpr uint32_t kTagBase = 0x7F810000u;             // tag of epoch e: kTagBase + e
-constexpr uint32_t kTagCount = 0x7FC00000u - kTagBase;  // epochs 0 .. kTagCount - 1
-// Half of the tags are in use while the other half is taken out of the workspace:
-// the first call of a half clears every slot that carries a tag of the other.
+constexpr uint32_t kTagCount = 0x7FC00000u - kTagBase;  // epochs 0 .. kTagCount - 1 (an even number)
+// While the tags of one half are in use those of the other are taken out of the
+// workspace: the call in the middle of a half clears every slot that carries a
+// tag of the other (the middle and not the start, so that a new workspace's
+// first call has nothing to clear).
 constexpr uint32_t kTagHalf = kTagCount / 2;
+constexpr uint32_t kTagClear = kTagHalf / 2;  // epoch modulo kTagHalf of that call
 
 // ---------------------------------------------------------------------------
 // kernel launchers (defined in the .hip files)

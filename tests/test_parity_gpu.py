@@ -503,8 +503,8 @@ def test_intermediate_values_hold_no_tag(T, act, sc):
 
 @pytest.mark.parametrize("kernel,T", [("decode", 1), ("mma", 8)])
 def test_tags_come_round(kernel, T):
-    # the epoch word moves on to 0 after the last tag; the first call of each half takes the other half's tags out of the
-    # workspace, so a value left from a call with the same tag is not taken for a fresh one
+    # the epoch word moves on to 0 after the last tag; the call in the middle of either half takes the other half's tags out
+    # of the workspace, so a value left from a call with the same tag is not taken for a fresh one
     big, small = (T, 4096, 1024, 144), (T, 512, 512, 80)
     b, s = _call(*big), _call(*small)
     ref_b, ref_s = (lb.lb_linear_forward(c[0], c[1], c[2], kernel=KERNELS[kernel]) for c in (b, s))
@@ -516,19 +516,22 @@ def test_tags_come_round(kernel, T):
         h = _high_words(ws)
         return int(((h >= TAG_BASE + lo) & (h < TAG_BASE + hi)).sum())
 
+    ctrl[0] = TAG_COUNT - 1
+    for after in (0, 1, 2):
+        assert torch.equal(lb.lb_linear_forward(s[0], s[1], s[2], workspace=ws, kernel=KERNELS[kernel]), ref_s)
+        assert int(ctrl[0]) == after
     x0 = b[0].clone()
-    for first, turn, after in ((5, half, half + 1), (half + 5, TAG_COUNT - 1, 1)):
+    for mine, other in ((0, half), (half, 0)):
         b[0].copy_(-2 * x0)
-        ctrl[0] = first
+        ctrl[0] = mine + 5
         lb.lb_linear_forward(b[0], b[1], b[2], workspace=ws, kernel=KERNELS[kernel])
-        assert int(ctrl[0]) == first + 1 and tags(first, first + 1) > 0
-        ctrl[0] = turn
-        for _ in range(2):
+        assert int(ctrl[0]) == mine + 6 and tags(mine + 5, mine + 6) > 0
+        for turn in (other + half // 2 - 1, other + half // 2):
+            ctrl[0] = turn
             assert torch.equal(lb.lb_linear_forward(s[0], s[1], s[2], workspace=ws, kernel=KERNELS[kernel]), ref_s)
-        assert int(ctrl[0]) == (turn + 2) % TAG_COUNT == after + (1 if turn == half else 0)
-        assert (tags(0, half) if turn == half else tags(half, TAG_COUNT - 1)) == 0
+            assert (tags(mine, mine + half) == 0) == (turn == other + half // 2)
         b[0].copy_(x0)
-        ctrl[0] = first
+        ctrl[0] = mine + 5
         assert torch.equal(lb.lb_linear_forward(b[0], b[1], b[2], workspace=ws, kernel=KERNELS[kernel]), ref_b)
     assert lb.lb_workspace_status(ws) == 0
 
