@@ -422,10 +422,10 @@ __host__ __device__ inline size_t frag_bytes(int T, int r, int nw) {
 // threads of R for one linear
 __host__ __device__ inline int r_items(int T, int r) { return 2 * ((T + 15) / 16) * nblocks32(r) * 64; }
 
-// ONE (one linear, few threads): a workgroup's 4 waves share the fragment,
-// each adding a quarter of the runs, and the quarters are added in order: the
-// sum is one round of loads instead of four (6.5 us at 16 runs).
-template <int NW, int SC, bool ONE>
+// SPLIT (few fragments): a workgroup's waves share a fragment, each adding a
+// share of the runs, and the shares are added in order: the sum is
+// one round of loads instead of four (6.5 us at 16 runs).
+template <int NW, int SC, int SPLIT>
 __device__ __forceinline__ void sm_r_body(const StreamLinear& L, int e) {
   const int T = L.T, r = L.r, s1d = L.s1d;
   if (e >= r_items(T, r)) return;
@@ -448,15 +448,15 @@ __device__ __forceinline__ void sm_r_body(const StreamLinear& L, int e) {
   }
   floatx4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
   const int wave = threadIdx.x >> 6;
-  const int per = (s1d + kWaves - 1) / kWaves;
-  const int c0 = ONE ? min(s1d, wave * per) : 0, c1 = ONE ? min(s1d, c0 + per) : s1d;
+  const int per = (s1d + SPLIT - 1) / SPLIT;
+  const int c0 = SPLIT > 1 ? min(s1d, wave * per) : 0, c1 = SPLIT > 1 ? min(s1d, c0 + per) : s1d;
 #pragma unroll 8
   for (int c = c0; c < c1; ++c) {
     z0 += *reinterpret_cast<const floatx4*>(src + c * cs);
     z1 += *reinterpret_cast<const floatx4*>(src + c * cs + hs);
   }
-  if constexpr (ONE) {
-    __shared__ floatx4 part[kWaves - 1][2][64];
+  if constexpr (SPLIT > 1) {
+    __shared__ floatx4 part[SPLIT - 1][2][64];
     if (wave > 0) {
       part[wave - 1][0][lane] = z0;
       part[wave - 1][1][lane] = z1;
@@ -464,7 +464,7 @@ __device__ __forceinline__ void sm_r_body(const StreamLinear& L, int e) {
     __syncthreads();
     if (wave > 0) return;
 #pragma unroll
-    for (int w = 0; w < kWaves - 1; ++w) {
+    for (int w = 0; w < SPLIT - 1; ++w) {
       z0 += part[w][0][lane];
       z1 += part[w][1][lane];
     }
@@ -483,13 +483,16 @@ __device__ __forceinline__ void sm_r_body(const StreamLinear& L, int e) {
                          lo[3][a] | (hi[3][a] << 16)};
 }
 
-template <int NW, int SC>
+// SPLIT = kWaves: a fragment per workgroup; 1: one per wave
+template <int NW, int SC, int SPLIT>
 __global__ void __launch_bounds__(kThreads) sm_r_kernel(const uint32_t* __restrict__ hdr,
                                                         const StreamLinear* __restrict__ descs,
                                                         const uint32_t* __restrict__ map, uint64_t fp) {
   if (!plan_ok(hdr, fp)) return;
   const uint32_t code = map[blockIdx.x];
-  sm_r_body<NW, SC, false>(descs[code >> 16], static_cast<int>(code & 0xffffu) * kThreads + threadIdx.x);
+  const int j = static_cast<int>(code & 0xffffu);
+  sm_r_body<NW, SC, SPLIT>(descs[code >> 16],
+                           SPLIT > 1 ? j * 64 + (threadIdx.x & 63) : j * kThreads + static_cast<int>(threadIdx.x));
 }
 
 // the bits st<DT> would store (16-bit dtypes)
@@ -514,9 +517,9 @@ __device__ __forceinline__ uint32_t round16(float v) {
 // ---------------------------------------------------------------------------
 constexpr int kBuf2 = 3;
 constexpr int kCk = 2;
-// row tiles per wave of the list kernels (fewer, larger workgroups up to 16
-// tokens, where a row tile takes 8 registers; 32 from 49 tokens)
-__host__ __device__ constexpr int rb_of(int tt) { return tt == 1 ? 8 : 4; }
+// row tiles per wave of the list kernels: 4, and up to 16 tokens, where a row
+// tile takes 8 registers (32 from 49 tokens), 8, or 2 in short lists
+__host__ __device__ constexpr int rb_of(int tt, bool shrt) { return tt == 1 ? (shrt ? 2 : 8) : 4; }
 
 // LDS of S2 (one array, as in S1): the fragment and U-word buffers, the 16-bit
 // tail words
@@ -705,13 +708,13 @@ __device__ __forceinline__ void sm_s2_body(const StreamLinear& L, int q) {
   }
 }
 
-template <int TT, int ACT, int SC>
+template <int TT, int RB, int ACT, int SC>
 __global__ void __launch_bounds__(kThreads) sm_s2_kernel(const uint32_t* __restrict__ hdr,
                                                          const StreamLinear* __restrict__ descs,
                                                          const uint32_t* __restrict__ map, uint64_t fp) {
   if (!plan_ok(hdr, fp)) return;
   const uint32_t code = map[blockIdx.x];
-  sm_s2_body<TT, rb_of(TT), ACT, SC, false>(descs[code >> 16], static_cast<int>(code & 0xffffu));
+  sm_s2_body<TT, RB, ACT, SC, false>(descs[code >> 16], static_cast<int>(code & 0xffffu));
 }
 
 // ---------------------------------------------------------------------------
@@ -743,41 +746,82 @@ void fill_desc(StreamLinear& L, const ForwardArgs& f, const SmGeom& g) {
   L.u_bytes = static_cast<uint32_t>(packed_bytes64(f.d_out, f.r));
 }
 
+// Lists too short to fill the chip with the workgroups that serve long ones best
+// (us a pass of 3 tokens, none of the three rules below -> all of them; 128-row
+// workgroups and one thread a latent, as before these stages, in brackets: a 7B
+// block 23.8 -> 15.7 (20.0), three 13B blocks 40.4 -> 29.0 (28.9), a 70B block 46.0 ->
+// 30.0 (27.9), two 54.5 -> 37.5 (41.1); 16 tokens, a 70B block 46.7 -> 30.1 (32.9)):
+//   S1  one launch per class of latent tiles is one after the other, and short
+//       ones leave the chip partly idle: below kOneClassWg1 workgroups they go out
+//       as one, of the largest class, unless that is over twice the tiles;
+//   S2  below kShortWg2 workgroups of 8 row tiles a wave, 2 row tiles (16 tokens);
+//   R   below kShortFrag fragments, four waves on each: a fragment's runs are read
+//       one after the other, 112 of them in a 70B down projection.
+constexpr int kOneClassWg1 = 4 * kWantWg1;
+constexpr int kShortWg2 = 512;
+constexpr int kShortFrag = 2048;
+
 struct PlanLayout {
   int bpr = kMaxBpr;
+  bool one_cls = false;  // one launch of S1 per token tile count, of its linears' largest class
+  bool short2 = false;   // S2 of 2 row tiles a wave (up to 16 tokens)
+  bool shortr = false;   // R of kWaves waves a fragment
+  int cls[4] = {};       // one_cls: that class
   int n1 = 0, nr = 0, n2 = 0;
   int n1_cls[4 * kMtClasses + 1] = {};  // S1 items of classes < k are map entries [0, n1_cls[k])
   int n2_cls[5] = {0, 0, 0, 0, 0};  // the same for S2 items
   size_t desc_off = 0, map1_off = 0, mapr_off = 0, map2_off = 0, data_off = 0, bytes = 0;
 };
 
-int r_groups(const ForwardArgs& a) { return (r_items(a.T, a.r) + kThreads - 1) / kThreads; }
-int s2_groups(const ForwardArgs& a) {
-  const int rw = 16 * kWaves * rb_of((a.T + 15) / 16);
+int r_groups(const ForwardArgs& a, bool shrt) {
+  const int n = shrt ? 64 : kThreads;
+  return (r_items(a.T, a.r) + n - 1) / n;
+}
+int s2_groups(const ForwardArgs& a, bool shrt) {
+  const int rw = 16 * kWaves * rb_of((a.T + 15) / 16, shrt);
   return (a.d_out + rw - 1) / rw;
 }
+// launch of S1: (tt - 1) kMtClasses + class
+int s1_launch(const PlanLayout& P, const SmGeom& g) { return P.one_cls ? (g.tt - 1) * kMtClasses + P.cls[g.tt - 1] : g.cls; }
 
 PlanLayout plan_layout(const ForwardArgs* a, int n) {
   PlanLayout P;
   // the longest runs (fewest partial sums) that still give kWantWg1 workgroups
   for (;; P.bpr /= 2) {
-    int64_t n1 = 0;
+    int64_t n1 = 0, n2 = 0, nf = 0, by_cls[4 * kMtClasses] = {};
     for (int i = 0; i < n; ++i)
       if (has_work(a[i])) {
         const SmGeom g = sm_geometry(a[i], P.bpr);
         n1 += 2 * g.ng * g.s1d;
+        by_cls[g.cls] += 2 * g.ng * g.s1d;
+        n2 += s2_groups(a[i], false);
+        nf += r_items(a[i].T, a[i].r) / 64;
       }
-    if (n1 >= kWantWg1 || P.bpr == kMinBpr) break;
+    if (n1 < kWantWg1 && P.bpr > kMinBpr) continue;
+    int64_t tiles = 0, tiles_one = 0;  // times token tiles, over S1's workgroups
+    for (int t = 0; t < 4; ++t) {
+      const int64_t* m = by_cls + t * kMtClasses;
+      for (int c = 0; c < kMtClasses; ++c)
+        if (m[c] > 0) P.cls[t] = c;
+      for (int c = 0; c < kMtClasses; ++c) {
+        tiles += m[c] * (t + 1) * mt_cls(t + 1, c);
+        tiles_one += m[c] * (t + 1) * mt_cls(t + 1, P.cls[t]);
+      }
+    }
+    P.one_cls = n1 < kOneClassWg1 && tiles_one <= 2 * tiles;
+    P.short2 = n2 < kShortWg2;
+    P.shortr = nf < kShortFrag;
+    break;
   }
   size_t data = 0;
   for (int i = 0; i < n; ++i) {
     if (!has_work(a[i])) continue;
     const SmGeom g = sm_geometry(a[i], P.bpr);
     P.n1 += 2 * g.ng * g.s1d;
-    P.n1_cls[g.cls + 1] += 2 * g.ng * g.s1d;
-    P.nr += r_groups(a[i]);
-    P.n2 += s2_groups(a[i]);
-    P.n2_cls[g.tt] += s2_groups(a[i]);
+    P.n1_cls[s1_launch(P, g) + 1] += 2 * g.ng * g.s1d;
+    P.nr += r_groups(a[i], P.shortr);
+    P.n2 += s2_groups(a[i], P.short2);
+    P.n2_cls[g.tt] += s2_groups(a[i], P.short2);
     data += align256(part_bytes(g)) + align256(frag_bytes(a[i].T, a[i].r, nw_of(a[i].act_dt)));
   }
   for (int k = 1; k <= 4 * kMtClasses; ++k) P.n1_cls[k] += P.n1_cls[k - 1];
@@ -809,13 +853,26 @@ void launch_s1(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stre
   launch_s1<TT, 3, ACT, SC>(b, P, fp, stream);
 }
 
-template <int TT, int ACT, int SC>
-void launch_s2(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stream) {
+template <int TT, int RB, int ACT, int SC>
+void launch_s2_rb(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stream) {
   const int n = P.n2_cls[TT] - P.n2_cls[TT - 1];
   if (n == 0) return;
-  hipLaunchKernelGGL((sm_s2_kernel<TT, ACT, SC>), dim3(n), dim3(kThreads), (S2Lds<TT, rb_of(TT), ACT>::kBytes), stream,
+  hipLaunchKernelGGL((sm_s2_kernel<TT, RB, ACT, SC>), dim3(n), dim3(kThreads), (S2Lds<TT, RB, ACT>::kBytes), stream,
                      reinterpret_cast<const uint32_t*>(b), reinterpret_cast<const StreamLinear*>(b + P.desc_off),
                      reinterpret_cast<const uint32_t*>(b + P.map2_off) + P.n2_cls[TT - 1], fp);
+}
+template <int TT, int ACT, int SC>
+void launch_s2(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stream) {
+  if (TT == 1 && P.short2)
+    launch_s2_rb<TT, rb_of(TT, TT == 1), ACT, SC>(b, P, fp, stream);
+  else
+    launch_s2_rb<TT, rb_of(TT, false), ACT, SC>(b, P, fp, stream);
+}
+template <int NW, int SC, int SPLIT>
+void launch_r(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stream) {
+  hipLaunchKernelGGL((sm_r_kernel<NW, SC, SPLIT>), dim3(P.nr), dim3(kThreads), 0, stream,
+                     reinterpret_cast<const uint32_t*>(b), reinterpret_cast<const StreamLinear*>(b + P.desc_off),
+                     reinterpret_cast<const uint32_t*>(b + P.mapr_off), fp);
 }
 
 template <int ACT, int SC>
@@ -825,9 +882,10 @@ void launch_all(const void* ws, const PlanLayout& P, uint64_t fp, hipStream_t st
   launch_s1<2, ACT, SC>(b, P, fp, stream);
   launch_s1<3, ACT, SC>(b, P, fp, stream);
   launch_s1<4, ACT, SC>(b, P, fp, stream);
-  hipLaunchKernelGGL((sm_r_kernel<nw_of(ACT), SC>), dim3(P.nr), dim3(kThreads), 0, stream,
-                     reinterpret_cast<const uint32_t*>(b), reinterpret_cast<const StreamLinear*>(b + P.desc_off),
-                     reinterpret_cast<const uint32_t*>(b + P.mapr_off), fp);
+  if (P.shortr)
+    launch_r<nw_of(ACT), SC, kWaves>(b, P, fp, stream);
+  else
+    launch_r<nw_of(ACT), SC, 1>(b, P, fp, stream);
   launch_s2<1, ACT, SC>(b, P, fp, stream);
   launch_s2<2, ACT, SC>(b, P, fp, stream);
   launch_s2<3, ACT, SC>(b, P, fp, stream);
@@ -900,10 +958,10 @@ hipError_t stream_mma_init(const ForwardArgs* a, int n, uint64_t fp, void* ws, h
     for (int p = 0; p < 2; ++p)
       for (int gr = 0; gr < g.ng; ++gr)
         for (int c = 0; c < g.s1d; ++c)
-          m1[i1[g.cls]++] = (static_cast<uint32_t>(i) << 16) | (p << 15) | (gr << 9) | c;
-    const int nrb = r_groups(f);
+          m1[i1[s1_launch(P, g)]++] = (static_cast<uint32_t>(i) << 16) | (p << 15) | (gr << 9) | c;
+    const int nrb = r_groups(f, P.shortr);
     for (int j = 0; j < nrb; ++j) mr[ir++] = (static_cast<uint32_t>(i) << 16) | j;
-    const int nrow = s2_groups(f);
+    const int nrow = s2_groups(f, P.short2);
     for (int j = 0; j < nrow; ++j) m2[i2[g.tt - 1]++] = (static_cast<uint32_t>(i) << 16) | j;
   }
   hipError_t e = hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, stream);
@@ -953,7 +1011,7 @@ __global__ void __launch_bounds__(kOneThreads) sm_one_s1_kernel(FewArgs A) {
 template <int NW, int SC>
 __global__ void __launch_bounds__(kThreads) sm_one_r_kernel(FewArgs A) {
   const StreamLinear& L = A.l[blockIdx.y];
-  sm_r_body<NW, SC, true>(L, blockIdx.x * 64 + (threadIdx.x & 63));
+  sm_r_body<NW, SC, kWaves>(L, blockIdx.x * 64 + (threadIdx.x & 63));
 }
 template <int TT, int ACT, int SC>
 __global__ void __launch_bounds__(kOneThreads) sm_one_s2_kernel(FewArgs A) {

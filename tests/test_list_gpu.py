@@ -263,3 +263,61 @@ def test_mma_list_tile_edges(act, sc):
     L.forward()
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(first, ys))
+
+
+# ---------------------------------------------------------------------------
+# matrix-core plans of longer lists: what they choose is computed here as the library's comments state it
+# ---------------------------------------------------------------------------
+def _classes(T):
+    tt = (T + 15) // 16
+    return tt, (2, 3, 5, 8 if tt <= 2 else 6)
+
+
+def _plan(specs):
+    """(blocks per run, S1 workgroups, latent tiles computed with a class per linear, with one class per token tile count)"""
+    for bpr in (64, 32, 16, 8):
+        n1, per, largest = 0, [], {}
+        for T, d_in, _, r in specs:
+            tt, cls = _classes(T)
+            nmf, nbt = -(-r // 16), -(-d_in // 32)
+            ng = -(-nmf // (4 * cls[-1]))
+            mt = next(c for c in cls if c >= -(-nmf // (4 * ng)))
+            n = 2 * ng * -(-nbt // bpr)
+            n1 += n
+            per.append((n * tt, tt, mt))
+            largest[tt] = max(largest.get(tt, 0), mt)
+        if n1 >= 1024 or bpr == 8:
+            return bpr, n1, sum(n * m for n, _, m in per), sum(n * largest[t] for n, t, _ in per)
+
+
+# (T, d_in, d_out, r) of every token tile count, rows of d_in past 2048 with tails; the first fills stage 2 (512 workgroups of
+# 512 rows) when the list is long
+LONG = [(5, 4100, 10000, 100), (16, 2052, 70, 513), (31, 2076, 130, 321), (48, 4108, 65, 385), (64, 2060, 257, 577)]
+
+
+@pytest.mark.parametrize("bpr,copies", [(64, 27), (32, 20), (16, 12), (8, 2)])
+@pytest.mark.parametrize("act,sc", [("bf16", "f16"), ("f32", "f32")])
+def test_mma_list_run_lengths(bpr, copies, act, sc):
+    assert _plan(LONG * copies)[0] == bpr
+    lins = _linears(LONG, cfg=46, act=act, sc=sc)
+    # copies of the linears with outputs of their own: the first is checked, the others have its bits
+    L, ys = _run_list(lins * copies)
+    for i, (li, _, _) in enumerate(lins):
+        tokens = None if li.T <= 16 else np.arange(0, li.T, 5)
+        _check(li, U.torch_to_raw(ys[i], act), tokens=tokens, label=f"mma list {LONG[i]} x{copies} {act}/{sc}")
+        for c in range(1, copies):
+            assert _same_bits(ys[i], ys[c * len(LONG) + i]), (LONG[i], c)
+
+
+@pytest.mark.parametrize("T", [3, 17, 33, 49])
+@pytest.mark.parametrize("act,sc", [("bf16", "f16"), ("f32", "f32")])
+def test_mma_list_class_launches(T, act, sc):
+    # many linears of few latents beside some of many: a launch of stage 1 per class; one of them alone: one launch
+    wide = [(T, 96, 40, 192), (T, 100, 41, 320), (T, 64, 42, 512 if T <= 32 else 384)]
+    for specs, apart in (([(T, 96, 33, 16), (T, 68, 30, 33)] * 4 + wide, True), (wide, False)):
+        _, _, tiles, tiles_one = _plan(specs)
+        assert (tiles_one > 2 * tiles) == apart
+        lins = _linears(specs, cfg=47, act=act, sc=sc)
+        _, ys = _run_list(lins)
+        for i, ((li, _, _), y) in enumerate(zip(lins, ys)):
+            _check(li, U.torch_to_raw(y, act), label=f"mma list {specs[i]} {act}/{sc}")
