@@ -11,7 +11,8 @@
 //   role V  (the reduction index runs down the rows): a thread builds one word,
 //           32 loads a row apart, lanes over the latent columns;
 //   role U  (it runs along a row): a wave takes 16 rows x 64 latents, a load a
-//           row; the compare's lane mask is that row's two words.
+//           row; the compare's lane mask is that row's two words.  Narrow
+//           rows would leave most lanes idle: 64 rows as one stream of elements.
 #include "device_common.h"
 
 namespace lb {
@@ -20,6 +21,12 @@ namespace {
 
 constexpr int kPackThreads = 256;
 constexpr int kPackRows = 16;  // role U: rows per wave
+// Role U, us for rows of r latents by 16 x 64 tiles against 64 rows a wave (bf16;
+// fp32 alike): 11008 rows r = 1 3.2 / 2.4, r = 8 3.2 / 2.8, r = 16 3.2 / 3.7, r = 32
+// 3.2 / 4.7; 262144 rows r = 1 10.1 / 2.5, r = 8 10.1 / 3.3, r = 16 9.9 / 4.7, r = 32 10.1 / 6.5
+constexpr int kNarrow = 8;                // rows of at most this: 64 a wave
+constexpr int kNarrowMany = 32;           // the same from kNarrowRows rows
+constexpr int kNarrowRows = 1 << 17;
 
 // word kb of output row o: a full word, or the tail plane's 16- or 32-bit entry
 __device__ __forceinline__ void put_word(uint32_t* dst, int kb, int o, int nb, int w, int n_out, uint32_t word) {
@@ -88,9 +95,57 @@ __global__ void __launch_bounds__(kPackThreads) pack_u_kernel(const void* __rest
   if (nan_count && nan) atomicAdd(nan_count, nan);
 }
 
+// r <= N (at most 32), so a row is one word or tail entry: a wave takes 64 rows,
+// whose 64 r elements are read 64 consecutive ones at a time; the compare's r lane
+// masks are 64 r consecutive bits, of which lane l takes those from l r on.
+template <int DT, int N>
+__global__ void __launch_bounds__(kPackThreads) pack_u_narrow_kernel(const void* __restrict__ src, int rows, int r,
+                                                                     uint32_t* __restrict__ dst, int32_t* nan_count) {
+  const int lane = threadIdx.x & 63;
+  const int64_t o0 = (blockIdx.x * static_cast<int64_t>(kPackThreads / 64) + (threadIdx.x >> 6)) * 64;
+  if (o0 >= rows) return;  // whole waves leave together
+  const int nrow = static_cast<int>(min(static_cast<int64_t>(64), rows - o0));
+  uint32_t e[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i < r) e[i] = ld_bits<DT>(src, o0 * r + (64 * i + lane < nrow * r ? 64 * i + lane : 0));
+  uint64_t mask = 0;  // lane i: of elements 64 i .. 64 i + 63
+  int nan = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i < r) {
+      const float v = bits_to_f32<DT>(e[i]);
+      const bool in = 64 * i + lane < nrow * r;
+      const uint64_t m = __ballot(in && v < 0.0f);
+      if (lane == i) mask = m;
+      nan += in && v != v;
+    }
+  const int w = (lane * r) >> 6, sh = (lane * r) & 63;
+  uint64_t bits = static_cast<uint64_t>(__shfl(static_cast<unsigned long long>(mask), w)) >> sh;
+  const uint64_t next = __shfl(static_cast<unsigned long long>(mask), (w + 1) & 63);
+  if (sh + r > 64) bits |= next << (64 - sh);
+  const uint32_t word = static_cast<uint32_t>(bits & ((uint64_t(1) << r) - 1));
+  if (lane < nrow) {
+    if (r <= 16)
+      reinterpret_cast<uint16_t*>(dst)[o0 + lane] = static_cast<uint16_t>(word);
+    else
+      dst[o0 + lane] = word;
+  }
+  if (nan_count && nan) atomicAdd(nan_count, nan);
+}
+
 template <int DT>
 void launch_pack_t(const void* src, int rows, int r, int role, uint32_t* dst, int32_t* nan_count, hipStream_t stream) {
-  if (role == LB_ROLE_U) {
+  if (role == LB_ROLE_U && (r <= kNarrow || (r <= kNarrowMany && rows >= kNarrowRows))) {
+    const int64_t waves = (int64_t(rows) + 63) / 64, per = kPackThreads / 64;
+    const dim3 grid(static_cast<uint32_t>((waves + per - 1) / per));
+    if (r <= kNarrow)
+      hipLaunchKernelGGL((pack_u_narrow_kernel<DT, kNarrow>), grid, dim3(kPackThreads), 0, stream, src, rows, r, dst,
+                         nan_count);
+    else
+      hipLaunchKernelGGL((pack_u_narrow_kernel<DT, kNarrowMany>), grid, dim3(kPackThreads), 0, stream, src, rows, r, dst,
+                         nan_count);
+  } else if (role == LB_ROLE_U) {
     const int64_t waves = static_cast<int64_t>((rows + kPackRows - 1) / kPackRows) * ((r + 63) / 64);
     const int64_t per = kPackThreads / 64;
     hipLaunchKernelGGL((pack_u_kernel<DT>), dim3(static_cast<uint32_t>((waves + per - 1) / per)), dim3(kPackThreads),

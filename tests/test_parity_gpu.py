@@ -89,6 +89,27 @@ def test_pack_tile_edges(rows, r, dt):
         assert int(cnt.item()) == nans == 1
 
 
+@pytest.mark.parametrize("rows,r", [(1, 1), (63, 1), (255, 2), (257, 5), (4097, 8), (1000, 15), (513, 16), (513, 17),
+                                    (63, 9), (131072, 9), (131073, 16), (131135, 17), (131130, 31), (131136, 32), (131072, 33)])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_pack_narrow_rows(rows, r, dt):
+    # rows of up to 8 latents, or 32 from 131072 rows on (64 of them as one stream of elements), and the first that are not,
+    # NaNs and infinities at the ends of rows
+    rs = np.random.default_rng(rows + r)
+    src64 = rs.standard_normal((rows, r))
+    src64[-1, -1] = np.nan
+    src64[0, 0] = -np.inf
+    if rows > 2:
+        src64[rows // 2, r - 1] = np.nan
+    raw = synth.quantize(src64, dt)
+    src_t = U.raw_to_torch(raw, dt)
+    cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+    got = lb.lb_pack_signs(src_t, lb.LB_ROLE_U, nan_count=cnt)
+    ref, nans = O.pack(O.to_f64(raw, dt), O.ROLE_U)
+    assert got.cpu().numpy().tobytes() == ref.tobytes()
+    assert int(cnt.item()) == nans
+
+
 def test_pack_nan_count():
     src = torch.randn(64, 48, device="cuda")
     src[3, 5] = float("nan")
