@@ -44,7 +44,7 @@ __global__ void __launch_bounds__(kPackThreads) pack_v_kernel(const void* __rest
                                                               uint32_t* __restrict__ dst, int32_t* nan_count) {
   const int nb = rows >> 5, w = rows & 31;
   const int64_t item = blockIdx.x * static_cast<int64_t>(kPackThreads) + threadIdx.x;
-  if (item >= static_cast<int64_t>(nblocks32(rows)) * r) return;
+  if (item >= static_cast<int64_t>(nb + (w != 0)) * r) return;
   const int kb = static_cast<int>(item / r), o = static_cast<int>(item - static_cast<int64_t>(kb) * r);
   const int width = kb < nb ? 32 : w;
   const int64_t base = static_cast<int64_t>(32 * kb) * r + o;
@@ -67,31 +67,32 @@ __global__ void __launch_bounds__(kPackThreads) pack_v_kernel(const void* __rest
 template <int DT>
 __global__ void __launch_bounds__(kPackThreads) pack_u_kernel(const void* __restrict__ src, int rows, int r,
                                                               uint32_t* __restrict__ dst, int32_t* nan_count) {
-  const int nb = r >> 5, w = r & 31;
+  const int nb = r >> 5, w = r & 31, nkb = nb + (w != 0);
   const int lane = threadIdx.x & 63;
-  const int nch = (r + 63) >> 6;  // 64-latent chunks
+  const int nch = (nkb + 1) >> 1;  // 64-latent chunks
   const int64_t unit = blockIdx.x * static_cast<int64_t>(kPackThreads / 64) + (threadIdx.x >> 6);
   const int64_t o0l = unit / nch * kPackRows;
   if (o0l >= rows) return;  // whole waves leave together
   const int o0 = static_cast<int>(o0l), c = static_cast<int>(unit % nch);
   const int nrow = min(kPackRows, rows - o0);
-  const int k = 64 * c + lane;
+  const uint32_t k = 64u * c + lane;
+  const uint32_t ur = r;
   uint32_t e[kPackRows];
 #pragma unroll
   for (int i = 0; i < kPackRows; ++i)
-    e[i] = ld_bits<DT>(src, i < nrow && k < r ? static_cast<int64_t>(o0 + i) * r + k : 0);
+    e[i] = ld_bits<DT>(src, i < nrow && k < ur ? (o0l + i) * r + k : 0);
   // lane 16 j + i: word 2 c + j of row o0 + i
   uint32_t word = 0;
   int nan = 0;
 #pragma unroll
   for (int i = 0; i < kPackRows; ++i) {
     const float v = bits_to_f32<DT>(e[i]);
-    const uint64_t m = __ballot(k < r && v < 0.0f);
+    const uint64_t m = __ballot(k < ur && v < 0.0f);
     if ((lane & 15) == i) word = static_cast<uint32_t>(lane & 16 ? m >> 32 : m);
-    nan += i < nrow && k < r && v != v;
+    nan += i < nrow && k < ur && v != v;
   }
   const int kb = 2 * c + (lane >> 4), i = lane & 15;
-  if (lane < 32 && i < nrow && kb < nblocks32(r)) put_word(dst, kb, o0 + i, nb, w, rows, word);
+  if (lane < 32 && i < nrow && kb < nkb) put_word(dst, kb, o0 + i, nb, w, rows, word);
   if (nan_count && nan) atomicAdd(nan_count, nan);
 }
 
@@ -146,12 +147,12 @@ void launch_pack_t(const void* src, int rows, int r, int role, uint32_t* dst, in
       hipLaunchKernelGGL((pack_u_narrow_kernel<DT, kNarrowMany>), grid, dim3(kPackThreads), 0, stream, src, rows, r, dst,
                          nan_count);
   } else if (role == LB_ROLE_U) {
-    const int64_t waves = static_cast<int64_t>((rows + kPackRows - 1) / kPackRows) * ((r + 63) / 64);
+    const int64_t waves = (int64_t(rows) + kPackRows - 1) / kPackRows * ((int64_t(r) + 63) / 64);
     const int64_t per = kPackThreads / 64;
     hipLaunchKernelGGL((pack_u_kernel<DT>), dim3(static_cast<uint32_t>((waves + per - 1) / per)), dim3(kPackThreads),
                        0, stream, src, rows, r, dst, nan_count);
   } else {
-    const int64_t items = static_cast<int64_t>(nblocks32(rows)) * r;
+    const int64_t items = (int64_t(rows) + 31) / 32 * r;
     hipLaunchKernelGGL((pack_v_kernel<DT>), dim3(static_cast<uint32_t>((items + kPackThreads - 1) / kPackThreads)),
                        dim3(kPackThreads), 0, stream, src, rows, r, dst, nan_count);
   }

@@ -110,6 +110,30 @@ def test_pack_narrow_rows(rows, r, dt):
     assert int(cnt.item()) == nans
 
 
+@pytest.mark.parametrize("rows,r", [((1 << 30) + 5, 1), ((1 << 31) - 1, 1), (1, (1 << 31) - 33), (1, (1 << 31) - 1)])
+@pytest.mark.parametrize("role", ["U", "V"])
+def test_pack_sizes_near_the_limit(rows, r, role):
+    # sizes whose tiles or threads do not fit 32 bits: element e of the other dimension's only one is bit e % 32 of word e / 32
+    # (rows, r) = (n, 1) in role V and (1, n) in role U; in the other two every entry has one bit, 16 bits wide
+    n = rows * r
+    src = torch.zeros(n, dtype=torch.bfloat16, device="cuda")
+    where = torch.tensor([0, 1, 31, 32, 63, 64, n // 2, n - 65, n - 64, n - 34, n - 33, n - 17, n - 16, n - 2, n - 1], device="cuda")
+    src[where] = -1.0
+    dst = lb.lb_pack_signs(src.view(rows, r), {"U": lb.LB_ROLE_U, "V": lb.LB_ROLE_V}[role])
+    del src
+    if (rows == 1) == (role == "U"):
+        nb, w = n // 32, n % 32
+        full, tail = dst[:4 * nb].view(torch.int32), dst[4 * nb:].view(torch.int16 if w <= 16 else torch.int32)
+        bits = [32 * i + b for v in (full,) for i in v.nonzero().flatten().tolist() for b in range(32) if (int(v[i]) >> b) & 1]
+        bits += [32 * nb + b for b in range(w) if w and (int(tail[0]) >> b) & 1]
+        assert bits == sorted(set(where.tolist()))
+    else:
+        v = dst.view(torch.int16)
+        assert v.numel() == n
+        at = torch.cat([s + k for k, s in ((k, v[k:k + (1 << 28)].nonzero().flatten()) for k in range(0, n, 1 << 28))])
+        assert torch.equal(at, where.unique()) and bool((v[at] == 1).all())
+
+
 def test_pack_nan_count():
     src = torch.randn(64, 48, device="cuda")
     src[3, 5] = float("nan")
