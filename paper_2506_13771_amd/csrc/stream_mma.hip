@@ -753,11 +753,14 @@ void fill_desc(StreamLinear& L, const ForwardArgs& f, const SmGeom& g) {
 // 30.0 (27.9), two 54.5 -> 37.5 (41.1); 16 tokens, a 70B block 46.7 -> 30.1 (32.9)):
 //   S1  one launch per class of latent tiles is one after the other, and short
 //       ones leave the chip partly idle: below kOneClassWg1 workgroups they go out
-//       as one, of the largest class, unless that is over twice the tiles;
+//       as one, of the largest class, unless that is over twice the tiles or more than
+//       kOneClassTiles idle ones over the blocks (16 70B blocks, 49000: 167 -> 156 us
+//       at 16 tokens; 32 7B blocks at 0.55 bits, 196000: f16 377 -> 397);
 //   S2  below kShortWg2 workgroups of 8 row tiles a wave, 2 row tiles (16 tokens);
 //   R   below kShortFrag fragments, four waves on each: a fragment's runs are read
 //       one after the other, 112 of them in a 70B down projection.
 constexpr int kOneClassWg1 = 4 * kWantWg1;
+constexpr int kOneClassTiles = 65536;
 constexpr int kShortWg2 = 512;
 constexpr int kShortFrag = 2048;
 
@@ -798,17 +801,17 @@ PlanLayout plan_layout(const ForwardArgs* a, int n) {
         nf += r_items(a[i].T, a[i].r) / 64;
       }
     if (n1 < kWantWg1 && P.bpr > kMinBpr) continue;
-    int64_t tiles = 0, tiles_one = 0;  // times token tiles, over S1's workgroups
+    int64_t tiles = 0, tiles_one = 0;  // over S1's workgroups
     for (int t = 0; t < 4; ++t) {
       const int64_t* m = by_cls + t * kMtClasses;
       for (int c = 0; c < kMtClasses; ++c)
         if (m[c] > 0) P.cls[t] = c;
       for (int c = 0; c < kMtClasses; ++c) {
-        tiles += m[c] * (t + 1) * mt_cls(t + 1, c);
-        tiles_one += m[c] * (t + 1) * mt_cls(t + 1, P.cls[t]);
+        tiles += m[c] * mt_cls(t + 1, c);
+        tiles_one += m[c] * mt_cls(t + 1, P.cls[t]);
       }
     }
-    P.one_cls = n1 < kOneClassWg1 && tiles_one <= 2 * tiles;
+    P.one_cls = n1 < kOneClassWg1 && tiles_one <= 2 * tiles && (tiles_one - tiles) * P.bpr <= kOneClassTiles;
     P.short2 = n2 < kShortWg2;
     P.shortr = nf < kShortFrag;
     break;

@@ -284,7 +284,7 @@ def _plan(specs):
             mt = next(c for c in cls if c >= -(-nmf // (4 * ng)))
             n = 2 * ng * -(-nbt // bpr)
             n1 += n
-            per.append((n * tt, tt, mt))
+            per.append((n, tt, mt))
             largest[tt] = max(largest.get(tt, 0), mt)
         if n1 >= 1024 or bpr == 8:
             return bpr, n1, sum(n * m for n, _, m in per), sum(n * largest[t] for n, t, _ in per)
