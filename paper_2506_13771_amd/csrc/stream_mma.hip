@@ -330,9 +330,16 @@ __device__ __forceinline__ void sm_s1_body(const StreamLinear& L, int p, int grp
     }
   };
   // fp32 inputs: the sums of kFold blocks are added apart, so that a run of 64
-  // blocks does not add 576 products' rounding to one accumulator (a list at 5.9e-7
-  // of the 64-bit result instead of 4.6e-7; 16-bit outputs round far above that)
-  constexpr int kFold = ACT == kDtF32 && !ONE ? (TT == 1 ? 4 : (TT == 2 ? 8 : 16)) : 0;
+  // blocks does not add 576 products' rounding to one accumulator.  Error
+  // against 64 bits (unfolded; folds of 4, 8 and 16 blocks for 1, 2 and more token
+  // tiles; these; runs of 4 to 16 blocks an accumulator split over four waves): 70B
+  // at 0.55 bits, 64 tokens 5.9e-7, 5.0e-7, 4.4e-7, 4.9e-7; 13B at 0.55, 31 tokens
+  // -, 4.04e-7, 3.80e-7, 4.02e-7; 13B at 0.1, 16 tokens -, 2.6e-7, 2.2e-7, 2.5e-7.
+  // They cost 1-2% of a pass, 4% at 17 to 32 tokens.  bf16 and f16 lists of 4 to 64
+  // tokens lie as far from the 64-bit result without folds as with ones of 2 to 8
+  // blocks (to 6 digits; those took 1-8% longer): their outputs' rounding is far
+  // above that of the sums.
+  constexpr int kFold = ACT == kDtF32 && !ONE ? (TT == 1 ? 2 : (TT == 2 ? 6 : 12)) : 0;
   floatx4 tot[kFold > 0 ? MT * TT : 1] = {};
   constexpr int kAhead = kBuf - 2;  // chunks still in flight when one is used
   int buf = 0;
