@@ -147,7 +147,7 @@ lb_kernel auto_kernel(int64_t T, int64_t d_in, int64_t d_out, int64_t r) {
 //            17.6 against 16.4 at 64; 8192 -> 28672, r = 304, T = 64: 28.4 against 27.5
 //            (larger output units); fp32 16384 -> 4096, r = 100, T = 64: 38 against 33
 //            (x is read once per 16 or 48 latents), 13824 -> 5120, r = 224 37.3 against 39.1.
-bool prefer_few(const lb::ForwardArgs& a, size_t need) {
+bool prefer_few(const lb::ForwardArgs& a, size_t need, lb::FewPlan& plan) {
   if (a.T <= kAutoLutTokens || a.T > 64) return false;
   const int64_t rd_in = static_cast<int64_t>(a.r) * a.d_in, rd_out = static_cast<int64_t>(a.r) * a.d_out;
   const bool f32 = a.act_dt == lb::kDtF32;
@@ -161,7 +161,7 @@ bool prefer_few(const lb::ForwardArgs& a, size_t need) {
   else
     few = (rd_in >= 15000 || (f32 && a.T <= 48)) &&
           !(a.T > 48 && (a.d_out > 16384 || (f32 && a.d_in >= 10000 && a.r <= 256)));
-  return few && lb::few_tokens_supports(a, need);
+  return few && lb::few_tokens_plan(a, need, plan);
 }
 
 }  // namespace
@@ -298,8 +298,9 @@ lb_status lb_linear_forward_kernel(const void* x, lb_dtype act_dtype, int64_t T,
     // three on the matrix-core decode kernel, then the prefill kernels
     kernel = auto_kernel(T, d_in, d_out, r);
     if (kernel == LB_KERNEL_AUTO) return LB_ERR_SHAPE;
-    if (prefer_few(a, need)) {
-      e = lb::launch_few_tokens(&a, &need, 1, stream);
+    lb::FewPlan plan;
+    if (prefer_few(a, need, plan)) {
+      e = lb::launch_few_tokens(&a, &plan, 1, stream);
       return e == hipSuccess ? LB_OK : LB_ERR_HIP;
     }
   }
@@ -412,11 +413,9 @@ bool auto_unsupported(const lb_linear_desc& d) {
   return has_work(d) && auto_kernel(d.T, d.d_in, d.d_out, d.r) == LB_KERNEL_AUTO;
 }
 
-// a linear AUTO runs by the few-token stages
-bool runs_few(const lb_linear_desc& d) {
-  return has_work(d) && auto_kernel(d.T, d.d_in, d.d_out, d.r) != LB_KERNEL_AUTO &&
-         prefer_few(make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, nullptr, 0),
-                    lb_forward_workspace_bytes(d.T, d.d_in, d.d_out, d.r));
+// a linear (a its arguments, need its workspace bytes) AUTO runs by the few-token stages
+bool runs_few(const lb_linear_desc& d, const lb::ForwardArgs& a, size_t need, lb::FewPlan& plan) {
+  return has_work(d) && auto_kernel(d.T, d.d_in, d.d_out, d.r) != LB_KERNEL_AUTO && prefer_few(a, need, plan);
 }
 
 // the list launch another linear joins: the look-up-table or the matrix-core
@@ -502,12 +501,12 @@ lb_status lb_linear_forward_many(const lb_linear_desc* descs, int64_t n, void* w
   // pair of dtypes to a launch of each stage (nothing depends on their order)
   struct FewBatch {
     lb::ForwardArgs a[lb::kFewMaxBatch];
-    size_t bytes[lb::kFewMaxBatch];
+    lb::FewPlan plan[lb::kFewMaxBatch];
     int n = 0;
   } few[4];
   auto flush_few = [&](FewBatch& f) -> lb_status {
     if (f.n == 0) return LB_OK;
-    const hipError_t e = lb::launch_few_tokens(f.a, f.bytes, f.n, stream);
+    const hipError_t e = lb::launch_few_tokens(f.a, f.plan, f.n, stream);
     f.n = 0;
     return e == hipSuccess ? LB_OK : LB_ERR_HIP;
   };
@@ -515,17 +514,20 @@ lb_status lb_linear_forward_many(const lb_linear_desc* descs, int64_t n, void* w
   size_t off = lb::kListHdrBytes;
   for (int64_t i = 0; i < n; ++i) {
     const lb_linear_desc& d = descs[i];
-    const size_t sb = slice_bytes(d);
+    const size_t need_i = lb_forward_workspace_bytes(d.T, d.d_in, d.d_out, d.r), sb = align256(need_i);
     const lb_kernel k = list_kernel(d);
-    if (runs_few(d)) {
+    const lb::ForwardArgs a =
+        make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, ws + off, sb);
+    lb::FewPlan plan;
+    if (runs_few(d, a, need_i, plan)) {
       FewBatch& f = few[(d.T + 15) / 16 - 1];
       if (f.n > 0 && (f.n == lb::kFewMaxBatch || static_cast<int>(d.act_dtype) != f.a[0].act_dt ||
                       static_cast<int>(d.scale_dtype) != f.a[0].sc_dt)) {
         const lb_status st = flush_few(f);
         if (st != LB_OK) return st;
       }
-      f.a[f.n] = make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, ws + off, sb);
-      f.bytes[f.n++] = lb_forward_workspace_bytes(d.T, d.d_in, d.d_out, d.r);
+      f.a[f.n] = a;
+      f.plan[f.n++] = plan;
     } else if (k != LB_KERNEL_AUTO) {
       if (nb > 0 && (nb == lb::kDecodeMaxBatch || k != bk || static_cast<int>(d.act_dtype) != batch[0].act_dt ||
                      static_cast<int>(d.scale_dtype) != batch[0].sc_dt)) {
@@ -533,7 +535,7 @@ lb_status lb_linear_forward_many(const lb_linear_desc* descs, int64_t n, void* w
         if (st != LB_OK) return st;
       }
       bk = k;
-      batch[nb] = make_args(d.x, d.act_dtype, d.T, d.d_in, d.d_out, d.r, d.paths, d.scale_dtype, d.y, ws + off, sb);
+      batch[nb] = a;
       // one control block for the whole list: the start of its workspace
       batch[nb].ctrl = workspace;
       batch[nb++].ctrl_bytes = workspace_bytes;

@@ -62,10 +62,7 @@ __host__ __device__ constexpr int mt_cls(int tt, int c) {
   return c == 0 ? 2 : (c == 1 ? 3 : (c == 2 ? 5 : (tt <= 2 ? 8 : 6)));
 }
 
-struct SmGeom {
-  int tt, nmf, ng, mt, bpr, s1d;
-  int cls;  // launch of S1: (tt - 1) kMtClasses + class
-};
+using SmGeom = FewPlan;  // cls: launch of S1, (tt - 1) kMtClasses + class
 
 // bpr: 32-input blocks per run wanted
 SmGeom sm_geometry(const ForwardArgs& a, int bpr) {
@@ -1126,18 +1123,20 @@ hipError_t one_sc(int sc_dt, const FewArgs& A, int n, int tt, int c, int n1, int
 
 }  // namespace
 
-bool few_tokens_supports(const ForwardArgs& a, size_t ws_bytes) {
-  return stream_mma_supports(a) && has_work(a) && ws_bytes > kScratchOff && one_geometry(a, ws_bytes).bpr > 0;
+bool few_tokens_plan(const ForwardArgs& a, size_t ws_bytes, FewPlan& g) {
+  if (!stream_mma_supports(a) || !has_work(a) || ws_bytes <= kScratchOff) return false;
+  g = one_geometry(a, ws_bytes);
+  return g.bpr > 0;
 }
 
-hipError_t launch_few_tokens(const ForwardArgs* a, const size_t* ws_bytes, int n, hipStream_t stream) {
+hipError_t launch_few_tokens(const ForwardArgs* a, const FewPlan* plans, int n, hipStream_t stream) {
   if (n < 1 || n > kFewMaxBatch) return hipErrorInvalidValue;
   FewArgs A{};
   const int tt = (a[0].T + 15) / 16;
   int c = 0, n1 = 0, nr = 0, n2 = 0;  // the largest tile class and grids
   for (int i = 0; i < n; ++i) {
     if ((a[i].T + 15) / 16 != tt || a[i].act_dt != a[0].act_dt || a[i].sc_dt != a[0].sc_dt) return hipErrorInvalidValue;
-    const SmGeom g = one_geometry(a[i], ws_bytes[i]);
+    const FewPlan& g = plans[i];
     StreamLinear& L = A.l[i];
     fill_desc(L, a[i], g);
     char* data = static_cast<char*>(a[i].ws) + kScratchOff;
