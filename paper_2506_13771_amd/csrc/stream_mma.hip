@@ -923,7 +923,8 @@ bool stream_mma_supports(const ForwardArgs& a) {
   const int64_t rows = 16 * ((a.T + 15) / 16);
   if ((rows + 1) * a.d_in * ex >= lim || packed_bytes64(a.d_out, a.r) >= lim || packed_bytes64(a.r, a.d_in) >= lim)
     return false;
-  // at most kMaxRuns runs of 16, 32 or 64 blocks (by token tiles)
+  // d_in: 511 runs of 16, 32 or 64 blocks by token tiles (the plan's runs, of up
+  // to 64 blocks whatever the tiles, need less)
   const int tt = (a.T + 15) / 16;
   if (nblocks32(a.d_in) > kMaxRuns * (tt == 1 ? 16 : (tt == 2 ? 32 : 64))) return false;
   // map codes: 16 bits of work index per linear
@@ -1030,8 +1031,10 @@ __global__ void __launch_bounds__(kOneThreads) sm_one_s2_kernel(FewArgs A) {
 constexpr int kOneWantWg = 192;  // S1 workgroups wanted
 constexpr int kOneMaxRuns = 16;  // runs at most: R adds them
 constexpr int kOneMinBpr = 8;    // 32-input blocks of a run at least: two per wave group
-// largest tile class of a 16-wave workgroup (128 registers a lane)
-constexpr int one_max_cls(int tt) { return tt == 1 ? 3 : (tt == 2 ? 2 : 1); }
+// largest tile class: 3 tiles a wave (from r = 961 and 16 runs; more tiles never give kOneWantWg)
+constexpr int kOneMaxCls = 1;
+static_assert(2 * ((kMaxRank / 16 + kWaves * mt_cls(1, 2) - 1) / (kWaves * mt_cls(1, 2))) * kOneMaxRuns < kOneWantWg,
+              "a larger class would be chosen");
 
 // the plan of one linear in ws_bytes of workspace (bpr 0: none fits): as many
 // runs as give kOneWantWg workgroups, fewer tiles a wave when they do not
@@ -1041,7 +1044,7 @@ SmGeom one_geometry(const ForwardArgs& a, size_t ws_bytes) {
   const size_t room = ws_bytes - kScratchOff;
   const size_t frag = align256(frag_bytes(a.T, a.r, nw_of(a.act_dt)));
   const int max_runs = std::max(1, std::min(kOneMaxRuns, nbt / kOneMinBpr));
-  int c = one_max_cls(g.tt);
+  int c = kOneMaxCls;
   for (;; --c) {
     g.ng = (g.nmf + kWaves * mt_cls(g.tt, c) - 1) / (kWaves * mt_cls(g.tt, c));
     if (c == 0 || 2 * g.ng * max_runs >= kOneWantWg) break;
@@ -1089,15 +1092,7 @@ hipError_t one_launch(const FewArgs& A, int n, int c, int n1, int nr, int n2, hi
   static std::atomic<bool> done{false};
   hipError_t e = allow_lds(&sm_one_s2_kernel<TT, ACT, SC>, bytes, done);
   if (e != hipSuccess) return e;
-  constexpr int most = one_max_cls(TT);
-  if (c == 0)
-    e = one_s1<TT, 0, ACT, SC>(A, n, n1, stream);
-  else if (c == 1)
-    e = one_s1<TT, 1, ACT, SC>(A, n, n1, stream);
-  else if (c == 2)
-    e = one_s1<TT, (most < 2 ? most : 2), ACT, SC>(A, n, n1, stream);
-  else
-    e = one_s1<TT, most, ACT, SC>(A, n, n1, stream);
+  e = c == 0 ? one_s1<TT, 0, ACT, SC>(A, n, n1, stream) : one_s1<TT, kOneMaxCls, ACT, SC>(A, n, n1, stream);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((sm_one_r_kernel<nw_of(ACT), SC>), dim3(nr, n), dim3(kThreads), 0, stream, A);
   hipLaunchKernelGGL((sm_one_s2_kernel<TT, ACT, SC>), dim3(n2, n), dim3(kOneThreads), bytes, stream, A);

@@ -676,7 +676,6 @@ __global__ __launch_bounds__(kCholThreads) void chol_orth_kernel(double* L, doub
 constexpr int kFacThreads = 1024;
 constexpr int kTl = 16;                  // tile edge
 constexpr int kTile = kTl * kTl;
-constexpr int kFacRows = 48;             // panel rows per wave (lanes 16-63)
 
 __host__ __device__ __forceinline__ int tri_lo(int i, int j) { return ((i * (i + 1)) >> 1) + j; }
 int chol_tiles(int b) { return (b + kTl - 1) / kTl; }

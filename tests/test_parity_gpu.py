@@ -422,7 +422,7 @@ def test_graph_replays_match_eager(T, kernel):
 
 
 # ---------------------------------------------------------------------------
-# the few-token stages (AUTO, 16 to 64 tokens; fewer where r d_out >= 8e6)
+# the few-token stages (AUTO, 3 to 64 tokens; by sizes: test_auto_rule)
 # ---------------------------------------------------------------------------
 # tile classes and groups of latents at their edges, one run and several, runs whose wave groups get unequal shares of
 # blocks, tails of d_in and r, rows that are not whole 16-byte pieces, outputs around the 64-row workgroups
@@ -438,6 +438,28 @@ def test_few_tokens_edges(case, act, sc):
     li = synth.make_linear(d_in, d_out, r, T, act_dtype=act, scale_dtype=sc, cfg=91, linear=T + d_in, l_over_sqrt_r=True)
     y_raw = _run(li)
     _check(li, y_raw, label=f"{case} {act}/{sc}")
+
+
+# as above, with sizes that AUTO gives to these stages in fp32 and in 16 bits, in fp32 seen from the result (every kernel adds in
+# an order of its own): both tile classes (2 tiles a wave; from r = 961 and 128 blocks of d_in 3), their first and last
+# rank, all token tile counts, tails of d_in and r
+FEW_TAKEN = [(16, 640, 65, 129), (17, 2092, 63, 33), (31, 4096, 33, 961), (16, 4096, 65, 961), (3, 4100, 127, 976),
+             (8, 4124, 1024, 1008), (32, 4108, 130, 1008), (48, 4096, 65, 1024), (64, 4100, 70, 970), (49, 5000, 1, 1009),
+             (64, 4092, 70, 961), (64, 2048, 64, 960), (33, 320, 129, 385), (48, 4128, 40, 960)]
+
+
+@pytest.mark.parametrize("case", FEW_TAKEN, ids=[f"T{c[0]}_{c[1]}x{c[2]}r{c[3]}" for c in FEW_TAKEN])
+@pytest.mark.parametrize("act,sc", [("bf16", "f16"), ("f32", "f32")])
+def test_few_tokens_classes(case, act, sc):
+    T, d_in, d_out, r = case
+    li = synth.make_linear(d_in, d_out, r, T, act_dtype=act, scale_dtype=sc, cfg=95, linear=T + d_in, l_over_sqrt_r=True)
+    x, paths, _ = U.to_device(li, True)
+    y = lb.lb_linear_forward(x, paths, r)
+    _check(li, U.torch_to_raw(y, act), label=f"{case} {act}/{sc}")
+    if act == "f32":
+        for k in ("mma", "prefill"):
+            if k == "prefill" or r <= 832:
+                assert not torch.equal(y, lb.lb_linear_forward(x, paths, r, kernel=KERNELS[k])), k
 
 
 def test_few_tokens_many_and_shared_workspace():
