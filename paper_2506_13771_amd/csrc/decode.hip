@@ -50,7 +50,6 @@
 //    and the workspace needs no clearing between calls.  No other call's
 //    intermediate values look like a tag, and tags are cleared from the
 //    workspace before they come round again (end_call).
-#include <atomic>
 #include <type_traits>
 
 #include "lut_common.h"
@@ -548,25 +547,16 @@ inline bool own_builders(const DecodeParams& P) {
 template <int TM, int ACT, int SC, bool VEC, int WPL, typename A>
 hipError_t launch_one(const A& args, dim3 grid, size_t smem, hipStream_t stream) {
   constexpr bool kOne = std::is_same<A, DecodeParams>::value;
-  // more than the default dynamic LDS limit: raise the kernel's limit once per
-  // size increase, so calls captured in a graph after an eager call of the
-  // same shape make no attribute call
-  static std::atomic<size_t> limit{65536};
-  if (smem > limit.load()) {
-    hipError_t e = hipSuccess;
-    if constexpr (kOne) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<TM, ACT, SC, VEC, WPL, false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
-      if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<TM, ACT, SC, VEC, WPL, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
-    } else {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_batch_kernel<TM, ACT, SC, VEC, WPL>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
-    }
-    if (e != hipSuccess) return e;
-    limit.store(smem);
+  static LdsLimit limit, limit_own;
+  hipError_t e;
+  if constexpr (kOne) {
+    e = own_builders(args)
+            ? raise_lds(reinterpret_cast<const void*>(&decode_kernel<TM, ACT, SC, VEC, WPL, true>), smem, limit_own)
+            : raise_lds(reinterpret_cast<const void*>(&decode_kernel<TM, ACT, SC, VEC, WPL, false>), smem, limit);
+  } else {
+    e = raise_lds(reinterpret_cast<const void*>(&decode_batch_kernel<TM, ACT, SC, VEC, WPL>), smem, limit);
   }
+  if (e != hipSuccess) return e;
   if constexpr (kOne) {
     if (own_builders(args))
       hipLaunchKernelGGL((decode_kernel<TM, ACT, SC, VEC, WPL, true>), grid, dim3(kThreads), smem, stream, args);
@@ -579,16 +569,11 @@ hipError_t launch_one(const A& args, dim3 grid, size_t smem, hipStream_t stream)
     } else {
       // stage 1 alone: its tables of TM tokens are all the LDS it needs
       constexpr size_t smem1 = sizeof(float) * TM * kChunk * kBlk;
-      static std::atomic<size_t> limit1{65536};
-      if (smem1 > limit1.load()) {
-        const hipError_t e =
-            hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_batch_s1_kernel<TM, ACT, SC, VEC>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem1));
-        if (e != hipSuccess) return e;
-        limit1.store(smem1);
-      }
+      static LdsLimit limit1;
+      e = raise_lds(reinterpret_cast<const void*>(&decode_batch_s1_kernel<TM, ACT, SC, VEC>), smem1, limit1);
+      if (e != hipSuccess) return e;
       hipLaunchKernelGGL((decode_batch_s1_kernel<TM, ACT, SC, VEC>), dim3(s1), dim3(kThreads), smem1, stream, args);
-      const hipError_t e = hipGetLastError();
+      e = hipGetLastError();
       if (e != hipSuccess || static_cast<int>(grid.x) <= s1) return e;
       DecodeBatch b2 = args;
       b2.wg0 = s1;

@@ -40,7 +40,6 @@
 // highest run of each tile first adds the others ("two-level").  Waits only
 // target lower block ids and are bounded; the epoch / done-counter protocol
 // is the same.
-#include <atomic>
 #include <type_traits>
 
 #include "device_common.h"
@@ -519,17 +518,11 @@ __global__ void __launch_bounds__(kThreads, 1) decode_mma_batch_kernel(MmaBatch 
 template <int TT, int ACT, int SC, bool VEC, typename A>
 hipError_t launch_one(const A& args, dim3 grid, size_t smem, hipStream_t stream) {
   constexpr bool kOne = std::is_same<A, MmaParams>::value;
-  // more than the default dynamic LDS limit (the CU has 160 KB): raise the
-  // kernel's limit once per size increase, so calls captured in a graph after
-  // an eager call of the same shape make no attribute call
-  static std::atomic<size_t> limit{65536};
-  if (smem > limit.load()) {
-    const void* fn = kOne ? reinterpret_cast<const void*>(&decode_mma_kernel<TT, ACT, SC, VEC>)
-                          : reinterpret_cast<const void*>(&decode_mma_batch_kernel<TT, ACT, SC, VEC>);
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
-    if (e != hipSuccess) return e;
-    limit.store(smem);
-  }
+  static LdsLimit limit;  // (the CU has 160 KB)
+  const hipError_t e = raise_lds(kOne ? reinterpret_cast<const void*>(&decode_mma_kernel<TT, ACT, SC, VEC>)
+                                      : reinterpret_cast<const void*>(&decode_mma_batch_kernel<TT, ACT, SC, VEC>),
+                                 smem, limit);
+  if (e != hipSuccess) return e;
   if constexpr (kOne)
     hipLaunchKernelGGL((decode_mma_kernel<TT, ACT, SC, VEC>), grid, dim3(kThreads), smem, stream, args);
   else

@@ -3,8 +3,19 @@
 // before any is waited on, and conversions.
 #pragma once
 #include "lb_internal.h"
+#include "lds_limit.h"
 
 namespace lb {
+
+// the limit of kernel fn, for a launch with `bytes` of dynamic LDS
+inline hipError_t raise_lds(const void* fn, size_t bytes, LdsLimit& limit) {
+  return static_cast<hipError_t>(limit.raise(
+      bytes, [](int* dev) { return static_cast<int>(hipGetDevice(dev)); },
+      [fn](size_t b) {
+        return static_cast<int>(
+            hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(b)));
+      }));
+}
 
 // Polls of a tagged slot before a wait gives up and records an error.
 constexpr uint32_t kSpinLimit = 1u << 19;

@@ -44,7 +44,6 @@
 // by 15 - 2 v moves the pair onto the two bf16 sign bits.  P2 uses the
 // relabelled order of sign_terms (its B operand is produced by P1b in that
 // order).
-#include <atomic>
 
 #include "device_common.h"
 #include "lb_backward.h"
@@ -890,25 +889,10 @@ __global__ void __launch_bounds__(kThreads2, 1) prefill_p2(PrefillParams P) {
   }
 }
 
-template <typename K>
-hipError_t raise_lds_limit(K* fn, size_t bytes, std::atomic<size_t>& limit) {
-  // more than the default dynamic LDS limit: raise the kernel's limit once per
-  // size increase, so calls captured in a graph after an eager call of the
-  // same shape make no attribute call
-  if (bytes > limit.load()) {
-    const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            static_cast<int>(bytes));
-    if (e != hipSuccess) return e;
-    limit.store(bytes);
-  }
-  return hipSuccess;
-}
-
 template <int MS, int ACT, int SC, bool VW, bool XV>
 hipError_t launch_p1v(const PrefillParams& P, const PrefillGeom& g, hipStream_t stream) {
-  static std::atomic<size_t> limit{65536};
-  hipError_t e = raise_lds_limit(&prefill_p1<MS, ACT, SC, VW, XV>, g.smem1, limit);
+  static LdsLimit limit;
+  hipError_t e = raise_lds(reinterpret_cast<const void*>(&prefill_p1<MS, ACT, SC, VW, XV>), g.smem1, limit);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((prefill_p1<MS, ACT, SC, VW, XV>), dim3(g.n_tt * g.n_lt * g.ks), dim3(kThreads1), g.smem1, stream,
                      P);
@@ -922,8 +906,8 @@ hipError_t launch_p1(const PrefillParams& P, const PrefillGeom& g, hipStream_t s
 
 template <int ACT, int SC, bool FAST>
 hipError_t launch_p2(const PrefillParams& P, const PrefillGeom& g, hipStream_t stream) {
-  static std::atomic<size_t> limit{65536};
-  hipError_t e = raise_lds_limit(&prefill_p2<ACT, SC, FAST>, g.smem2, limit);
+  static LdsLimit limit;
+  hipError_t e = raise_lds(reinterpret_cast<const void*>(&prefill_p2<ACT, SC, FAST>), g.smem2, limit);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((prefill_p2<ACT, SC, FAST>), dim3(g.n_og * g.n_tt2), dim3(kThreads2), g.smem2, stream, P);
   return hipGetLastError();

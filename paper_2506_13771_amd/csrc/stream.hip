@@ -29,7 +29,6 @@
 // written once by stream_init); every kernel first compares the plan's
 // fingerprint with the one of the call and does nothing but set bit 1 of the
 // error word if they differ.
-#include <atomic>
 #include <cstring>
 #include <vector>
 
@@ -456,12 +455,8 @@ void launch_s1_nt(const char* b, const PlanLayout& P, int cls, uint64_t fp, hipS
   const int n = P.n1_cls[cls + 1] - P.n1_cls[cls];
   const int rpad = ((P.rmax + 63) / 64) * 64;
   const size_t smem = sizeof(float) * (TM * MAXBLK * 128 + 4 * TM * rpad + P.rmax);
-  static std::atomic<size_t> limit{65536};
-  if (smem > limit.load()) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&stream_s1_kernel<TM, ACT, SC, MAXBLK, TAIL16, NTALL>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
-    limit.store(smem);
-  }
+  static LdsLimit limit;
+  (void)raise_lds(reinterpret_cast<const void*>(&stream_s1_kernel<TM, ACT, SC, MAXBLK, TAIL16, NTALL>), smem, limit);
   hipLaunchKernelGGL((stream_s1_kernel<TM, ACT, SC, MAXBLK, TAIL16, NTALL>), dim3(n), dim3(kThreads), smem, stream,
                      reinterpret_cast<const uint32_t*>(b), reinterpret_cast<const StreamLinear*>(b + P.desc_off),
                      reinterpret_cast<const uint32_t*>(b + P.map1_off) + P.n1_cls[cls], fp);

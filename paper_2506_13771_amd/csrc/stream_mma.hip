@@ -24,7 +24,6 @@
 // Inputs of this path: x and g read as aligned groups of four (d_in a
 // multiple of 4, x and g aligned to four elements).
 #include <algorithm>
-#include <atomic>
 #include <cstring>
 #include <vector>
 
@@ -1068,20 +1067,11 @@ SmGeom one_geometry(const ForwardArgs& a, size_t ws_bytes) {
   }
 }
 
-// a kernel with more than 64 KB of dynamic LDS: its limit is raised once
-template <typename K>
-hipError_t allow_lds(K* fn, int bytes, std::atomic<bool>& done) {
-  if (bytes <= 65536 || done.load()) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess) done.store(true);
-  return e;
-}
 template <int TT, int C, int ACT, int SC>
 hipError_t one_s1(const FewArgs& A, int n, int n1, hipStream_t stream) {
   constexpr int MT = mt_cls(TT, C), bytes = S1Lds<TT, MT, ACT, SC, true>::kBytes;
-  static std::atomic<bool> done{false};
-  const hipError_t e = allow_lds(&sm_one_s1_kernel<TT, MT, ACT, SC>, bytes, done);
+  static LdsLimit limit;
+  const hipError_t e = raise_lds(reinterpret_cast<const void*>(&sm_one_s1_kernel<TT, MT, ACT, SC>), bytes, limit);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((sm_one_s1_kernel<TT, MT, ACT, SC>), dim3(n1, n), dim3(kOneThreads), bytes, stream, A);
   return hipGetLastError();
@@ -1089,8 +1079,8 @@ hipError_t one_s1(const FewArgs& A, int n, int n1, hipStream_t stream) {
 template <int TT, int ACT, int SC>
 hipError_t one_launch(const FewArgs& A, int n, int c, int n1, int nr, int n2, hipStream_t stream) {
   constexpr int bytes = S2Lds<TT, 1, ACT, true>::kBytes;
-  static std::atomic<bool> done{false};
-  hipError_t e = allow_lds(&sm_one_s2_kernel<TT, ACT, SC>, bytes, done);
+  static LdsLimit limit;
+  hipError_t e = raise_lds(reinterpret_cast<const void*>(&sm_one_s2_kernel<TT, ACT, SC>), bytes, limit);
   if (e != hipSuccess) return e;
   e = c == 0 ? one_s1<TT, 0, ACT, SC>(A, n, n1, stream) : one_s1<TT, kOneMaxCls, ACT, SC>(A, n, n1, stream);
   if (e != hipSuccess) return e;

@@ -5,6 +5,7 @@ of these calls needs a GPU)."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -515,3 +516,52 @@ def test_list_validation(lib):
     assert lib.lb_list_forward(arr, 70000, FAKE, need, None) == lb.LB_ERR_ARG
     # the workspace grows with the list
     assert lib.lb_list_workspace_bytes(_list_descs(600), 600) > need
+
+
+LDS_LIMIT_DRIVER = r"""
+#include <cstdio>
+#include <thread>
+#include <vector>
+#include "lds_limit.h"
+// a kernel's attribute per device, as the runtime keeps it; calls: how often it was set
+static size_t attr[3];
+static int calls, dev_now, fail_set;
+static int device(int* d) { *d = dev_now; return 0; }
+static int set(size_t b) { ++calls; if (fail_set) return 1; attr[dev_now] = b; return 0; }
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
+int main() {
+  lb::LdsLimit l;
+  CHECK(l.raise(65536, device, set) == 0 && calls == 0);             // the default needs nothing
+  CHECK(l.raise(100000, device, set) == 0 && attr[0] == 100000);
+  dev_now = 1;
+  CHECK(l.raise(90000, device, set) == 0 && attr[1] == 90000);       // each device has its own
+  dev_now = 0;
+  CHECK(l.raise(90000, device, set) == 0 && attr[0] == 100000 && calls == 2);  // never lowered, set once
+  CHECK(l.raise(120000, device, set) == 0 && attr[0] == 120000 && calls == 3);
+  dev_now = 2, fail_set = 1;
+  CHECK(l.raise(70000, device, set) != 0);
+  fail_set = 0;
+  CHECK(l.raise(70000, device, set) == 0 && attr[2] == 70000);       // a failed call is not remembered
+  // threads that want different sizes leave the largest
+  lb::LdsLimit m;
+  static size_t largest;
+  auto set2 = [](size_t b) { largest = b; return 0; };
+  std::vector<std::thread> t;
+  for (int i = 0; i < 16; ++i) t.emplace_back([&m, &set2, i] { for (int k = 0; k < 1000; ++k) m.raise(66000 + 64 * ((i * 37 + k) % 1000), device, set2); });
+  for (auto& x : t) x.join();
+  CHECK(largest == 66000 + 64 * 999);
+  std::puts("ok");
+  return 0;
+}
+"""
+
+
+def test_lds_limit_per_device(tmp_path):
+    # the dynamic LDS limit is an attribute of a kernel on one device: a process that uses two raises both
+    src = tmp_path / "lds_limit.cpp"
+    src.write_text(LDS_LIMIT_DRIVER)
+    csrc = os.path.join(os.path.dirname(lb.__file__), "csrc")
+    exe = str(tmp_path / "lds_limit")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", csrc, str(src), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout
