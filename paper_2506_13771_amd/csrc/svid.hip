@@ -28,7 +28,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "lb_internal.h"
+#include "device_common.h"
 
 namespace lb {
 namespace {
@@ -1197,10 +1197,9 @@ struct Svid {
       const int smem = static_cast<int>(sizeof(double) * (full ? b * b : b * (b + 1) / 2));
       const void* fn = full ? reinterpret_cast<const void*>(&jacobi_log_kernel)
                             : reinterpret_cast<const void*>(&jacobi_log_packed_kernel);
-      if (smem > 65536) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
-      }
+      static LdsLimit limit, limit_packed;
+      const hipError_t e = raise_lds(fn, smem, full ? limit : limit_packed);
+      if (e != hipSuccess) return e;
       double2* rl = reinterpret_cast<double2*>(at(L.rlog));
       int* ns = reinterpret_cast<int*>(at(L.nsw));
       if (full)
@@ -1256,10 +1255,9 @@ struct Svid {
       const int smem = chol_smem_bytes(b);
       const void* solve = b <= 128 ? reinterpret_cast<const void*>(&chol_trsm_kernel<8>)
                                    : reinterpret_cast<const void*>(&chol_trsm_kernel<12>);
-      if (smem > 65536) {
-        for (const void* fn : {reinterpret_cast<const void*>(&chol_factor_kernel), solve})
-          if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, smem)) != hipSuccess) return e;
-      }
+      static LdsLimit limit, limit_solve[2];
+      if ((e = raise_lds(reinterpret_cast<const void*>(&chol_factor_kernel), smem, limit)) != hipSuccess) return e;
+      if ((e = raise_lds(solve, smem, limit_solve[b > 128])) != hipSuccess) return e;
       hipLaunchKernelGGL(chol_factor_kernel, dim3(1), dim3(kFacThreads), smem, st,
                          static_cast<const double*>(at(L.gram)), at(L.e), at(L.et), b);
       if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1285,11 +1283,8 @@ struct Svid {
     // the top eigenpair of |F|^T |F| (column 0 of E, lam[0])
     {
       const int smem = r <= kEigLdsMax ? static_cast<int>(sizeof(double) * r * r) : 0;
-      if (smem > 65536) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&top_eig_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
-      }
+      static LdsLimit limit;
+      if ((e = raise_lds(reinterpret_cast<const void*>(&top_eig_kernel), smem, limit)) != hipSuccess) return e;
       hipLaunchKernelGGL(top_eig_kernel, dim3(1), dim3(kEigThreads), smem, st, static_cast<const double*>(at(L.gram)),
                          at(L.e), at(L.lam), r);
       if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -565,3 +565,10 @@ def test_lds_limit_per_device(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", csrc, str(src), "-o", exe], check=True)
     out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout
+
+
+def test_lds_limits_through_one_record():
+    # an attribute set beside the record would lower what another thread has raised
+    csrc = os.path.join(os.path.dirname(lb.__file__), "csrc")
+    users = [f for f in sorted(os.listdir(csrc)) if "hipFuncSetAttribute" in open(os.path.join(csrc, f)).read()]
+    assert users == ["device_common.h"]
