@@ -11,7 +11,7 @@
 //   R   one thread per (linear, path, token tile, 32 latents, lane): w = l (.) z
 //       from the runs' partials in ascending run order, cut into bf16 terms and
 //       stored as stage 2's B operand;
-//   S2  one workgroup per (linear, 256 or 512 output rows): the B operands of both
+//   S2  one workgroup per (linear, 128 to 512 output rows): the B operands of both
 //       paths stream through LDS, shared by the 4 waves, each 32-latent block's
 //       A operand (U signs) is built once per row tile and serves every token
 //       tile, y = h_0 u_0 + h_1 u_1 rounded once (one launch per token tile
@@ -145,7 +145,7 @@ struct S1Lds {
   static constexpr int kRed = 2 * kWaves * MT * TT * 1024;  // ONE: two groups' sums, in place of the ring
   static constexpr int kRing = kVt + NWV * NV * 256;
   static constexpr int kBytes = ONE && kRed > kRing ? kRed : kRing;
-  static_assert(kBuf >= 2 && kBytes <= (ONE ? 160 * 1024 : 65536), "ring depth; no launch attribute for lists");
+  static_assert(kBuf >= 2 && kBytes <= (ONE ? 160 * 1024 : 65536), "ring depth; S1's lists raise no LDS limit");
 };
 
 template <int TT, int MT, int ACT, int SC, bool ONE>
@@ -863,7 +863,11 @@ template <int TT, int RB, int ACT, int SC>
 void launch_s2_rb(const char* b, const PlanLayout& P, uint64_t fp, hipStream_t stream) {
   const int n = P.n2_cls[TT] - P.n2_cls[TT - 1];
   if (n == 0) return;
-  hipLaunchKernelGGL((sm_s2_kernel<TT, RB, ACT, SC>), dim3(n), dim3(kThreads), (S2Lds<TT, RB, ACT>::kBytes), stream,
+  // (past 64 KB for 33 to 64 tokens in fp32; a failure is left to hipGetLastError)
+  constexpr int bytes = S2Lds<TT, RB, ACT>::kBytes;
+  static LdsLimit limit;
+  (void)raise_lds(reinterpret_cast<const void*>(&sm_s2_kernel<TT, RB, ACT, SC>), bytes, limit);
+  hipLaunchKernelGGL((sm_s2_kernel<TT, RB, ACT, SC>), dim3(n), dim3(kThreads), bytes, stream,
                      reinterpret_cast<const uint32_t*>(b), reinterpret_cast<const StreamLinear*>(b + P.desc_off),
                      reinterpret_cast<const uint32_t*>(b + P.map2_off) + P.n2_cls[TT - 1], fp);
 }
