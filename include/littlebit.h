@@ -74,9 +74,19 @@ typedef enum lb_role { LB_ROLE_U = 0, LB_ROLE_V = 1 } lb_role;
 
 /* Which forward kernel lb_linear_forward_kernel() runs. */
 typedef enum lb_kernel {
-  LB_KERNEL_AUTO = 0,         /* DECODE for T <= 2; from T = 3 DECODE_MFMA while T r d_out is
-                                 small (T < 16, or T < 32 with r d_out < 3e6, and r d_out < 8e6),
-                                 PREFILL otherwise (each where its size limits allow) */
+  LB_KERNEL_AUTO = 0,         /* DECODE for T <= 2.  For T = 3 .. 64 the few-token stages (three
+                                 launches of matrix-core tiles, which no code below names) where
+                                 d_in is a multiple of 4, x, g_0 and g_1 are aligned to four
+                                 elements, the workspace holds their plan and the layer is large
+                                 enough: r (d_in + d_out) >= 3.2e6 below 8 tokens; r d_out >= 1e6, or
+                                 d_in, d_out >= 4096 with r (d_in + d_out) >= 6e5, below 16; r d_in >=
+                                 7.5e4 at 16 tokens, 3e4 from 17, 1.5e4 from 24 (fp32: 4e4 from 17,
+                                 2e4 from 28); from 32 r d_in >= 1.5e4 (fp32: all sizes up to 48), past 48 only with
+                                 d_out <= 16384 (fp32: and d_in < 10000 or r > 256).  Else
+                                 DECODE_MFMA while T r d_out is small (T < 16, or T < 32 with
+                                 r d_out < 3e6, and r d_out < 8e6), PREFILL otherwise (each where its
+                                 size limits allow).  The bits of a result depend on the kernel, so
+                                 for T = 3 .. 64 on the alignment of x and g as well. */
   LB_KERNEL_DECODE = 1,       /* single launch, 4-bit look-up tables, fp32 sign-flip accumulation;
                                  T <= 4, r <= 1024 */
   LB_KERNEL_PREFILL = 2,      /* three launches of matrix-core (MFMA) tiles with exact bf16 term
@@ -193,8 +203,8 @@ lb_status lb_linear_forward(const void* x, lb_dtype act_dtype, int64_t T, int64_
    lb_noalloc_scratch_bytes() = 32 MiB per GPU, one copy per device, held until
    the process ends; the call allocates nothing (no hipMalloc, no allocating
    library routine).  Sizes whose lb_forward_workspace_bytes exceed the
-   scratch and the 4096 bytes of list counters return LB_ERR_WORKSPACE; other checks and results as for
-   lb_linear_forward (bit-identical to it).  The first call on a device
+   scratch and the 4096 bytes of list counters return LB_ERR_WORKSPACE; other
+   checks and results as for lb_linear_forward (bit-identical to it).  The first call on a device
    resolves that device's copy and enqueues its zero fill on `stream`; that
    first call must not be captured in a graph (LB_ERR_ARG), later ones may be.
    Every call on one GPU shares its scratch (the decode kernels keep their
@@ -240,10 +250,13 @@ size_t lb_forward_many_workspace_bytes(const lb_linear_desc* descs, int64_t n);
    computes it, Proposition 1 summed over both paths; the paper's end-to-end
    decoding measurement replaces every nn.Linear of the model by this
    forward, appendix "End-to-End Decoding Throughput"), enqueued on one
-   stream with fewer launches: consecutive linears for which the automatic
-   choice is the same decode kernel (look-up-table or matrix-core) and that
-   share the activation and scale dtypes run as one launch of that kernel per
-   up to 16 linears; every other linear (prefill sizes) is its own call with
+   stream with fewer launches: consecutive linears (those of the few-token
+   stages left out) for which the automatic choice is the same decode kernel
+   (look-up-table or matrix-core) and that share the activation and scale
+   dtypes run as one launch of that kernel per up to 16 linears; linears of the
+   few-token stages run as one launch of each stage per up to 8 of one token
+   tile count ((T + 15) / 16) and one pair of dtypes, possibly after linears
+   that follow them in the list; every other linear (prefill) is its own call with
    the automatic kernel choice.  Results are those of lb_linear_forward for each
    linear.  descs: host array of n descriptors (device pointers inside, as
    for lb_linear_forward).  No y may overlap another linear's x or y (they run

@@ -99,7 +99,8 @@ lb::ForwardArgs make_args(const void* x, lb_dtype act, int64_t T, int64_t d_in, 
 
 constexpr int64_t kAutoLutTokens = 2;  // AUTO sends T <= this to the look-up-table decode kernel
 
-// AUTO between the matrix-core decode kernel and the prefill kernels: the
+// AUTO between the matrix-core decode kernel and the prefill kernels, where
+// the few-token stages (prefer_few) do not take the call: the
 // decode kernel's single launch wins while T r d_out is small; the prefill
 // kernels' cost barely grows with T up to one 64-token tile.  Thresholds from
 // timings of both kernels on the Llama2-7B and -70B linear shapes (0.1 and
@@ -294,8 +295,9 @@ lb_status lb_linear_forward_kernel(const void* x, lb_dtype act_dtype, int64_t T,
     return e == hipSuccess ? LB_OK : LB_ERR_HIP;
   }
   if (kernel == LB_KERNEL_AUTO) {
-    // the look-up-table kernel is the fastest for one or two tokens; from
-    // three on the matrix-core decode kernel, then the prefill kernels
+    // the look-up-table kernel is the fastest for one or two tokens; from three
+    // to 64 the few-token stages where prefer_few says so, else the matrix-core
+    // decode kernel, then the prefill kernels
     kernel = auto_kernel(T, d_in, d_out, r);
     if (kernel == LB_KERNEL_AUTO) return LB_ERR_SHAPE;
     lb::FewPlan plan;

@@ -461,10 +461,11 @@ __device__ __forceinline__ void mma_stage2(const MmaParams& P, int q, float* sme
     __syncthreads();  // the next chunk reuses the LDS
   }
   if (!ok) atomic_store_relaxed(P.ctrl + kCtrlError, 1u);
-  // The last stage-2 workgroup to count itself moves the epoch on.  Every workgroup of this call has read the epoch by then: stage-2
-  // workgroups counted themselves after reading it, and every stage-1
-  // workgroup published values carrying the tag, which this workgroup has
-  // gathered (directly, or through the two-level reducers).
+  // The last stage-2 workgroup to count itself moves the epoch on.  Every
+  // workgroup of this call has read the epoch by then: stage-2 workgroups
+  // counted themselves after reading it, and every stage-1 workgroup published
+  // values carrying the tag, which this workgroup has gathered (directly, or
+  // through the two-level reducers).
   // In a list launch each linear counts its workgroups on a word of its own
   // (one contended word for all of them would serialise the atomics), and the
   // last workgroup of each linear counts that linear on the shared word.
