@@ -49,7 +49,7 @@
 //    consecutive calls, graph replays included, never confuse each other's slots
 //    and the workspace needs no clearing between calls.  No other call's
 //    intermediate values look like a tag, and tags are cleared from the
-//    workspace before they come round again (end_call).
+//    workspace before they come round again (note_slots).
 #include <type_traits>
 
 #include "lut_common.h"
@@ -210,7 +210,7 @@ __device__ void stage1(const DecodeParams& P, int wg, float* smem) {
       }
     }
   }
-  if (wg == 0 && tid == 0) note_slots(P.ctrl, P.span);
+  if (wg == 0 && tid < 64) note_slots(P.ctrl, epoch, P.span);
 }
 
 // ---------------------------------------------------------------------------
@@ -463,8 +463,7 @@ __device__ void stage2(const DecodeParams& P, int q2, float* smem) {
   // In a list launch each linear counts its workgroups on a word of its own
   // (one contended word for all of them would serialise the atomics), and the
   // last workgroup of each linear counts that linear on the shared word.
-  if (tid < 64)
-    end_call(P.ctrl, P.ctr, epoch, P.n_members, tid == 0 && done_before == static_cast<uint32_t>(P.n_s2 - 1), P.span);
+  if (tid == 0 && done_before == static_cast<uint32_t>(P.n_s2 - 1)) end_call(P.ctrl, P.ctr, epoch, P.n_members);
 }
 
 template <int TM, int ACT, int SC, bool VEC, int WPL, bool OWN>

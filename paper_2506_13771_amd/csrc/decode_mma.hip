@@ -272,7 +272,7 @@ __device__ __forceinline__ void mma_stage1(const MmaParams& P, int wg, float* sm
     }
     if (!ok) atomic_store_relaxed(P.ctrl + kCtrlError, 1u);
   }
-  if (wg == 0 && tid == 0) note_slots(P.ctrl, P.span);
+  if (wg == 0 && wave == 0) note_slots(P.ctrl, epoch, P.span);
 }
 
 // ---------------------------------------------------------------------------
@@ -469,8 +469,7 @@ __device__ __forceinline__ void mma_stage2(const MmaParams& P, int q, float* sme
   // In a list launch each linear counts its workgroups on a word of its own
   // (one contended word for all of them would serialise the atomics), and the
   // last workgroup of each linear counts that linear on the shared word.
-  if (wave == 0)
-    end_call(P.ctrl, P.ctr, epoch, P.n_members, tid == 0 && done_before == static_cast<uint32_t>(P.n_s2 - 1), P.span);
+  if (tid == 0 && done_before == static_cast<uint32_t>(P.n_s2 - 1)) end_call(P.ctrl, P.ctr, epoch, P.n_members);
 }
 
 template <int TT, int ACT, int SC, bool VEC>
